@@ -7,7 +7,7 @@
 namespace shw {
 
 constexpr int kMaxDm = 4;
-constexpr int kResidualChunk = 32;  // outputs per launch (origins travel in the kernel arguments)
+constexpr int kResidualChunk = 80;  // outputs per launch (their windows travel in the kernel arguments)
 
 struct DmLaunch {
   const int* grid;   // [(2m+1)^2] actuator index of grid cell (gy, gx), -1 if none; device
@@ -18,16 +18,25 @@ struct DmLaunch {
   float inv_2s2;     // 1 / (2 sigma^2)
 };
 
+// One residual output: element offsets of its windows' first pixels and its place in the result.
+struct ResidualOut {
+  int64_t scr_off;
+  int64_t dm_off[kMaxDm];
+  int64_t out;
+};
+
 struct ResidualLaunch {
   const float* screen;
   int64_t screen_pitch;
   const float* surf[kMaxDm];
   int32_t surf_size[kMaxDm];
-  int32_t n_dm;
-  int32_t pupil_n;
-  int32_t scr_origin[kResidualChunk][2];
-  int32_t dm_origin[kResidualChunk][kMaxDm][2];
+  int32_t n_out, pupil_n;
+  int32_t quads;            // ceil(pupil_n / 4)
+  int32_t per_block;        // outputs that one block goes through
+  int32_t xcd_tiles;        // 256-quad tiles per XCD
+  int32_t streaming;        // write the result past the caches
   int64_t out_pitch, out_stride;
+  ResidualOut o[kResidualChunk];
 };
 
 hipError_t launch_dm_surface(const DmLaunch& a, const float* coefs, float* surf, hipStream_t st);
@@ -46,6 +55,6 @@ hipError_t launch_influence_opd(const InfluenceLaunch& a, float* out, hipStream_
 // im[s * ld + m] = (slopes[2m][s] - slopes[2m+1][s]) * scale for m < n_modes, s < n_slopes.
 hipError_t launch_push_pull(const float* slopes, int32_t n_modes, int32_t n_slopes, float scale, float* im,
                             int64_t ld, hipStream_t st);
-hipError_t launch_residual(const ResidualLaunch& a, int n_out, float* out, hipStream_t st);
+hipError_t launch_residual(ResidualLaunch& a, int n_dm, float* out, hipStream_t st);
 
 }  // namespace shw

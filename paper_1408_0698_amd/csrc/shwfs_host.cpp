@@ -1044,7 +1044,6 @@ extern "C" int shw_residual_opd(const float* d_screen, int32_t screen_rows, int3
   ResidualLaunch a{};
   a.screen = d_screen;
   a.screen_pitch = screen_pitch;
-  a.n_dm = n_dm;
   a.pupil_n = pupil_n;
   a.out_pitch = out_pitch;
   a.out_stride = out_stride;
@@ -1052,17 +1051,31 @@ extern "C" int shw_residual_opd(const float* d_screen, int32_t screen_rows, int3
     a.surf[d] = d_surf[d];
     a.surf_size[d] = surf_size[d];
   }
-  for (int k0 = 0; k0 < n_out; k0 += kResidualChunk) {
-    const int nk = n_out - k0 < kResidualChunk ? n_out - k0 : kResidualChunk;
-    for (int k = 0; k < nk; ++k) {
-      a.scr_origin[k][0] = scr_origin[2 * (k0 + k)];
-      a.scr_origin[k][1] = scr_origin[2 * (k0 + k) + 1];
-      for (int d = 0; d < n_dm; ++d) {
-        a.dm_origin[k][d][0] = dm_origin[((k0 + k) * n_dm + d) * 2];
-        a.dm_origin[k][d][1] = dm_origin[((k0 + k) * n_dm + d) * 2 + 1];
-      }
+  // outputs with the same mirror windows next to each other (the kernel then reads the mirrors
+  // once for a run of them)
+  std::vector<ResidualOut> outs((size_t)n_out);
+  for (int k = 0; k < n_out; ++k) {
+    ResidualOut& o = outs[k];
+    o = ResidualOut{};
+    o.scr_off = (int64_t)scr_origin[2 * k] * screen_pitch + scr_origin[2 * k + 1];
+    o.out = k;
+    for (int d = 0; d < n_dm; ++d) {
+      const int32_t* w = dm_origin + ((int64_t)k * n_dm + d) * 2;
+      o.dm_off[d] = (int64_t)w[0] * surf_size[d] + w[1];
     }
-    hipError_t e = launch_residual(a, nk, d_out + (int64_t)k0 * out_stride, (hipStream_t)stream);
+  }
+  std::stable_sort(outs.begin(), outs.end(), [](const ResidualOut& u, const ResidualOut& v) {
+    for (int d = 0; d < kMaxDm; ++d)
+      if (u.dm_off[d] != v.dm_off[d]) return u.dm_off[d] < v.dm_off[d];
+    return false;
+  });
+  // launches of equal size
+  const int launches = (n_out + kResidualChunk - 1) / kResidualChunk;
+  for (int i = 0; i < launches; ++i) {
+    const int k0 = (int)((int64_t)n_out * i / launches), k1 = (int)((int64_t)n_out * (i + 1) / launches);
+    a.n_out = k1 - k0;
+    std::copy(outs.begin() + k0, outs.begin() + k1, a.o);
+    hipError_t e = launch_residual(a, n_dm, d_out, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "shw_residual_opd launch");
   }
   return ok();

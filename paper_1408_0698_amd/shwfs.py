@@ -9,6 +9,8 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+from array import array
+from itertools import chain
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(PKG, "lib", "libshwfs.so")
@@ -505,6 +507,18 @@ class DmPlan:
         return out
 
 
+def _int32s(values, n):
+    """int32 C array of n values (the rest 0).  array() converts a whole list at once, several times
+    faster than ctypes' own element loop; what it refuses (floats, wrapping integers) goes through int()."""
+    values = list(values)
+    if len(values) == n:
+        try:
+            return (C.c_int32 * n).from_buffer(array("i", values))
+        except (TypeError, OverflowError):
+            pass
+    return (C.c_int32 * n)(*[int(v) for v in values])
+
+
 def residual_opd(screen, surfaces, pupil_n, scr_origin, dm_origin, out, stream=None):
     """out[k] = screen window k - sum_d surface_d window (k, d).
 
@@ -515,8 +529,8 @@ def residual_opd(screen, surfaces, pupil_n, scr_origin, dm_origin, out, stream=N
     n_dm = len(surfaces)
     ptrs = (C.c_void_p * max(1, n_dm))(*[s.data_ptr() for s in surfaces])
     sizes = (C.c_int32 * max(1, n_dm))(*[s.shape[0] for s in surfaces])
-    so = (C.c_int32 * (2 * max(1, n_out)))(*[int(v) for o in scr_origin for v in o])
-    do = (C.c_int32 * (2 * max(1, n_out * n_dm)))(*[int(v) for o in dm_origin for dd in o for v in dd])
+    so = _int32s(chain.from_iterable(scr_origin), 2 * max(1, n_out))
+    do = _int32s(chain.from_iterable(chain.from_iterable(dm_origin)), 2 * max(1, n_out * n_dm))
     _check(_lib.shw_residual_opd(_ptr(screen), screen.shape[0], screen.shape[1], screen.stride(0), n_dm, ptrs, sizes,
                                  pupil_n, n_out, so, do, _ptr(out), out.stride(1), out.stride(0),
                                  _stream_ptr(stream)), "shw_residual_opd")

@@ -8,7 +8,7 @@
 namespace shw {
 
 constexpr int kMaxLayers = 16;
-constexpr int kProjectChunk = 32;  // targets per projection launch (their parameters travel in the arguments)
+constexpr int kUplinkChunk = 32;   // beams per uplink launch (their parameters travel in the arguments)
 constexpr int kMaxRadii = 64;      // encircled-energy radii per call
 constexpr int kEeGroups = 200;     // row groups of the encircled-energy pass
 
@@ -20,6 +20,7 @@ struct LayerDesc {
   int32_t rows, cols;
   int64_t pitch;
   double pitch_m, alt_m, x0, y0;
+  double inv_pitch;  // 1 / pitch_m
 };
 
 struct LayerSet {
@@ -29,13 +30,22 @@ struct LayerSet {
 
 // OPD of target t at pupil pixel (i, j) (centre (j + 1/2 - N/2, i + 1/2 - N/2) dx from the axis):
 // sum over layers of the bilinear screen sample at (1 - h/H) r + h theta, H the source altitude
-// (0: infinity), plus tilt[t] . r when tilt is set.
+// (0: infinity), plus tilt[t] . r when tilt is set.  In screen samples that point is
+// (ax + b (j + 1/2 - N/2), ay + b (i + 1/2 - N/2)), with a map for each target and layer.
+constexpr int kProjectMaps = 120;  // maps per launch (they travel in the arguments)
+struct ProjectLayer {
+  const float* screen;
+  int64_t pitch;
+  int32_t rows, cols;
+};
+struct ProjectMap {
+  double ax, ay, b;
+};
 struct ProjectLaunch {
-  LayerSet L;
-  int32_t pupil_n, n_t;
+  ProjectLayer layer[kMaxLayers];
+  ProjectMap map[kProjectMaps];  // [n_t][n_layers]
+  int32_t n_layers, n_t, pupil_n, pad0;
   double dx;
-  double theta[kProjectChunk][2];
-  double inv_h[kProjectChunk];   // 1 / source altitude, 0 for infinity
   const double* tilt;            // nullable [n_t][2] radians, already offset to the chunk
   float* out;                    // target t at out + t * out_stride
   int64_t out_pitch, out_stride;
@@ -47,7 +57,7 @@ hipError_t launch_project_layers(const ProjectLaunch& a, hipStream_t st);
 // launcher (1 - h/H) + h theta at altitude h.
 struct UplinkLaunch {
   LayerSet L;
-  double lgs[kProjectChunk][5];  // launcher x, y (m), theta x, y (rad), sodium altitude (m)
+  double lgs[kUplinkChunk][5];  // launcher x, y (m), theta x, y (rad), sodium altitude (m)
   int32_t n, n_s;
   double d;
   double* tilt;                  // [n][2] radians, already offset to the chunk

@@ -1440,6 +1440,7 @@ static int fill_layers(LayerSet& S, int32_t n_layers, const float* const* d_scre
     L.cols = cols[l];
     L.pitch = pitch[l];
     L.pitch_m = q[0];
+    L.inv_pitch = 1.0 / q[0];
     L.alt_m = q[1];
     L.x0 = q[2];
     L.y0 = q[3];
@@ -1462,8 +1463,8 @@ extern "C" int shw_project_layers(int32_t n_layers, const float* const* d_screen
                                   int32_t pupil_n, double dx_m, int32_t n_targets, const double* target_params,
                                   const double* d_tilt, float* d_out, int64_t out_pitch, int64_t out_stride,
                                   void* stream) {
-  ProjectLaunch a{};
-  int e = fill_layers(a.L, n_layers, d_screen, screen_rows, screen_cols, screen_pitch, layer_params);
+  LayerSet S;
+  int e = fill_layers(S, n_layers, d_screen, screen_rows, screen_cols, screen_pitch, layer_params);
   if (e != SHW_OK) return e;
   if (pupil_n < 1 || pupil_n > 16384) return fail(SHW_E_INVALID, "pupil_n %d outside [1, 16384]", pupil_n);
   if (!(is_fin(dx_m) && dx_m > 0)) return fail(SHW_E_INVALID, "dx_m must be > 0");
@@ -1478,7 +1479,7 @@ extern "C" int shw_project_layers(int32_t n_layers, const float* const* d_screen
     if (!is_fin(q[0]) || !is_fin(q[1]) || !(is_fin(q[2]) && q[2] >= 0))
       return fail(SHW_E_INVALID, "target %d: direction must be finite, altitude >= 0", t);
     for (int l = 0; l < n_layers; ++l) {
-      const LayerDesc& L = a.L.layer[l];
+      const LayerDesc& L = S.layer[l];
       if (q[2] > 0 && !(q[2] > L.alt_m)) return fail(SHW_E_INVALID, "target %d is not above layer %d", t, l);
       const double s = q[2] > 0 ? 1.0 - L.alt_m / q[2] : 1.0;
       const double cx = L.alt_m * q[0], cy = L.alt_m * q[1];
@@ -1486,19 +1487,28 @@ extern "C" int shw_project_layers(int32_t n_layers, const float* const* d_screen
         return fail(SHW_E_INVALID, "target %d: footprint leaves layer %d", t, l);
     }
   }
+  ProjectLaunch a{};
+  for (int l = 0; l < n_layers; ++l)
+    a.layer[l] = ProjectLayer{S.layer[l].screen, S.layer[l].pitch, S.layer[l].rows, S.layer[l].cols};
+  a.n_layers = n_layers;
   a.pupil_n = pupil_n;
   a.dx = dx_m;
   a.out_pitch = out_pitch;
   a.out_stride = out_stride;
   hipStream_t st = (hipStream_t)stream;
-  for (int t0 = 0; t0 < n_targets; t0 += kProjectChunk) {
-    const int nt = n_targets - t0 < kProjectChunk ? n_targets - t0 : kProjectChunk;
+  const int chunk = kProjectMaps / n_layers;
+  for (int t0 = 0; t0 < n_targets; t0 += chunk) {
+    const int nt = n_targets - t0 < chunk ? n_targets - t0 : chunk;
     a.n_t = nt;
     for (int k = 0; k < nt; ++k) {
       const double* q = target_params + 3 * (t0 + k);
-      a.theta[k][0] = q[0];
-      a.theta[k][1] = q[1];
-      a.inv_h[k] = q[2] > 0 ? 1.0 / q[2] : 0.0;
+      const double inv_h = q[2] > 0 ? 1.0 / q[2] : 0.0;
+      for (int l = 0; l < n_layers; ++l) {
+        const LayerDesc& L = S.layer[l];
+        const double h = L.alt_m * L.inv_pitch;
+        a.map[k * n_layers + l] = ProjectMap{L.x0 + h * q[0], L.y0 + h * q[1],
+                                             (1.0 - L.alt_m * inv_h) * dx_m * L.inv_pitch};
+      }
     }
     a.tilt = d_tilt ? d_tilt + 2 * t0 : nullptr;
     a.out = d_out + t0 * out_stride;
@@ -1538,8 +1548,8 @@ extern "C" int shw_uplink_tilt(int32_t n_layers, const float* const* d_screen, c
   a.n_s = n_samples;
   a.d = llt_diameter_m;
   hipStream_t st = (hipStream_t)stream;
-  for (int k0 = 0; k0 < n_lgs; k0 += kProjectChunk) {
-    const int nk = n_lgs - k0 < kProjectChunk ? n_lgs - k0 : kProjectChunk;
+  for (int k0 = 0; k0 < n_lgs; k0 += kUplinkChunk) {
+    const int nk = n_lgs - k0 < kUplinkChunk ? n_lgs - k0 : kUplinkChunk;
     a.n = nk;
     for (int k = 0; k < nk; ++k)
       for (int j = 0; j < 5; ++j) a.lgs[k][j] = lgs_params[5 * (k0 + k) + j];

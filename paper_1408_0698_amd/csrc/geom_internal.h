@@ -66,7 +66,7 @@ hipError_t launch_uplink_tilt(const UplinkLaunch& a, hipStream_t st);
 
 // Encircled energy of n_psf M x M PSFs: radii r_k (pixels, k < n_r) around (M/2, M/2).  Pass 1
 // writes, per PSF and row group g, the sums over the group's rows of the energy inside each
-// radius (ws [n_psf][kEeGroups][n_r + 1], the last entry the group's total); pass 2 adds the
+// radius (ws [n_psf][n_r + 1][kEeGroups], entry n_r the groups' totals); pass 2 adds the
 // groups in order and divides by the total.
 struct EeLaunch {
   const float* psf;

@@ -22,120 +22,141 @@ __device__ __forceinline__ int isqrt_floor(double q) {
   return w;
 }
 
-// Pass 1: block (g, s) takes rows g, g + G, ... of PSF s, one row per wavefront at a time.  For a
-// row at dv from the centre, the pixels within radius r form the run |u - c| <= w, w =
-// floor(sqrt(r^2 - dv^2)), whose share is pre(hi + 1) - pre(lo) of the row's FP64 prefix sums
-// pre.  The wavefront stages the row in LDS with coalesced loads; lane l sums its run of R
-// consecutive pixels (R a multiple of 8, 64 R >= M) in chunks of 8, a scan over the lanes gives the
-// runs' offsets, and the lanes write pre at every 8th pixel; a prefix is then one of those plus at
-// most 7 staged pixels.  Lane k < n_r keeps radius k's sum over the wavefront's rows, every lane
-// the rows' total; the block's wavefronts are added in a fixed order at the end.
-// LDS per wavefront: 65 doubles (the end), the row (pixel u at u + u/32, so that the lanes' runs
-// start in different banks), and pre at every 8th pixel (ceil(M/8) doubles).
-__device__ __forceinline__ void ee_wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
+// Pass 1.  The pixels within radius r of a row at dv from the centre c = M/2 form the run |u - c| <= w,
+// w = floor(sqrt(r^2 - dv^2)), the same for the rows c + dv and c - dv.  So the two rows are folded
+// about the centre first, G[j] = P[c + dv][c + j] + P[c + dv][c - j] + P[c - dv][c + j] + P[c - dv][c - j],
+// and their share of radius r is the prefix sum of G up to w: a quarter of the pixels to scan, one
+// window for both rows, one prefix instead of a difference of two.
+// A wavefront takes one pair of rows: lane l holds j = 256 i + 4 l .. 4 l + 3 (16-byte reads of both
+// sides of both rows, all in flight together), FP64 sums, a scan over the lanes for every i, and the
+// prefixes go to LDS, where lane k < n_r reads radius k's.  The column u = 0 of an even M (and any
+// other without a mirror image) has j past the folded part and is added to the windows that
+// reach it.  Block (g, s) takes the row distances g, g + G, ... of PSF s, one per wavefront at a time;
+// its wavefronts are added in a fixed order.
+// Bound by the read: 9 PSFs of 1600^2 (92 MB) take 21 us traced = 4.4 TB/s; a wavefront per single row,
+// staged in LDS and scanned whole, took 52 us.
+constexpr int kEeWaves = 4;
+constexpr int kEeSteps = 8;  // 256-pixel steps per half row: M <= 4096
+static_assert(kMaxRadii <= 64, "one lane per radius");
 
-__host__ __device__ constexpr int ee_row_slot(int u) { return u + (u >> 5); }
+// Pixels p .. p + 3 (16 bytes at 4-byte alignment).
+typedef float EeQuad __attribute__((ext_vector_type(4), aligned(4)));
 
-__host__ __device__ constexpr size_t ee_wave_lds(int m) {
-  return 65 * sizeof(double) + (size_t)((ee_row_slot(m) + 3) & ~3) * sizeof(float) +
-         (size_t)((m + 7) / 8) * sizeof(double);
-}
-
-constexpr int kEeMaxChunks = 8;  // chunks of 8 pixels per lane: 64 x 64 >= M for M <= 4096
-static_assert(kMaxRadii <= 64, "one lane per radius, entry n_r of the 65-double areas for the total");
-
-__global__ __launch_bounds__(256) void ee_rows_kernel(const EeLaunch a) {
-  extern __shared__ __align__(16) unsigned char ee_smem[];
-  const int M = a.m, c = M / 2;
-  const int R = ((M + 511) / 512) * 8;  // pixels per lane, a multiple of 8
-  const int nw = blockDim.x >> 6, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int g = blockIdx.x, s = blockIdx.y;
-  unsigned char* mine = ee_smem + (size_t)wave * ee_wave_lds(M);
-  double* fin = reinterpret_cast<double*>(mine);
-  float* srow = reinterpret_cast<float*>(mine + 65 * sizeof(double));
-  double* pre8 =
-      reinterpret_cast<double*>(mine + 65 * sizeof(double) + (size_t)((ee_row_slot(M) + 3) & ~3) * sizeof(float));
-  const float* P = a.psf + s * a.psf_stride;
-  const int u0 = lane * R;
-  double acc = 0.0, tot = 0.0;
-  for (int v = g + wave * kEeGroups; v < M; v += nw * kEeGroups) {
-    const float* row = P + (int64_t)v * M;
-    for (int u = lane; u < M; u += 64) srow[ee_row_slot(u)] = row[u];
-    ee_wave_sync();
-    double ch[kEeMaxChunks];
-    double run = 0.0;
+// Inclusive sums over the lanes of a wavefront, in a fixed order.
+__device__ __forceinline__ double ee_scan(double v, int lane) {
 #pragma unroll
-    for (int i = 0; i < kEeMaxChunks; ++i) {
-      const int k = u0 + 8 * i;
-      double cs = 0.0;
-      if (8 * i < R && k < M) {
-#pragma unroll
-        for (int t = 0; t < 8; ++t)
-          if (k + t < M) cs += (double)srow[ee_row_slot(k + t)];
-      }
-      ch[i] = cs;
-      run += cs;
-    }
-    double inc = run;  // inclusive scan over the lanes, the same tree for every row
-    for (int off = 1; off < 64; off <<= 1) {
-      const double t = __shfl_up(inc, off);
-      if (lane >= off) inc += t;
-    }
-    const double row_tot = __shfl(inc, 63);
-    double x = inc - run;  // pre at the lane's chunk starts
-#pragma unroll
-    for (int i = 0; i < kEeMaxChunks; ++i) {
-      const int k = u0 + 8 * i;
-      if (8 * i < R && k < M) pre8[k >> 3] = x;
-      x += ch[i];
-    }
-    ee_wave_sync();
-    tot += row_tot;
-    if (lane < a.n_r) {
-      const double dv = (double)(v - c);
-      const double rem = a.r2[lane] - dv * dv;
-      if (rem >= 0.0) {
-        const int w = isqrt_floor(rem);
-        const int lo = c - w < 0 ? 0 : c - w;
-        const int hi = c + w > M - 1 ? M - 1 : c + w;
-        auto prefix = [&](int p) -> double {  // pre(p), 0 <= p <= M
-          if (p == M) return row_tot;
-          const int k = p & ~7;
-          double y = pre8[k >> 3];
-#pragma unroll
-          for (int t = 0; t < 7; ++t)
-            if (k + t < p) y += (double)srow[ee_row_slot(k + t)];
-          return y;
-        };
-        acc += prefix(hi + 1) - prefix(lo);
-      }
-    }
-    ee_wave_sync();  // the staged row and pre8 are rewritten for the next row
+  for (int off = 1; off < 64; off <<= 1) {
+    const double t = __shfl_up(v, off);
+    if (lane >= off) v += t;
   }
-  // the wavefronts' sums in LDS, then added in wavefront order
-  if (lane < a.n_r) fin[lane] = acc;
-  if (lane == 0) fin[a.n_r] = tot;
+  return v;
+}
+
+// STEPS 256-pixel steps cover the folded half row (STEPS x 256 >= H).
+template <int STEPS>
+__global__ __launch_bounds__(64 * kEeWaves) void ee_rows_kernel(const EeLaunch a) {
+  extern __shared__ __align__(16) double ee_pre[];  // [wavefront][H rounded up to 4]
+  __shared__ double fin[kEeWaves][kMaxRadii + 1];
+  const int M = a.m, c = M / 2;
+  // folded part: j < H has both c + j and c - j inside the row, in whole quads; pixels beyond it are
+  // added one by one
+  const int H = ((M - c) < (c + 1) ? (M - c) : (c + 1)) & ~3;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int g = blockIdx.x, s = blockIdx.y;
+  double* pre = ee_pre + wave * H;
+  const float* P = a.psf + s * a.psf_stride;
+  const double r2 = lane < a.n_r ? a.r2[lane] : -1.0;
+  double acc = 0.0, tot = 0.0;
+  for (int dv = g + wave * kEeGroups; dv <= c; dv += kEeWaves * kEeGroups) {
+    // rows c + dv and c - dv, or the one of them that is there (dv = 0: the centre row once)
+    const bool pair = dv > 0 && c + dv < M;
+    const float* hi = P + (int64_t)(c + dv < M ? c + dv : c - dv) * M;
+    const float* lo = P + (int64_t)(c - dv) * M;
+    EeQuad q[STEPS][4];
+#pragma unroll
+    for (int i = 0; i < STEPS; ++i) {
+      const int j = 256 * i + 4 * lane;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) q[i][k] = EeQuad{0.0f, 0.0f, 0.0f, 0.0f};
+      if (j < H) {
+        q[i][0] = *reinterpret_cast<const EeQuad*>(hi + c + j);
+        q[i][1] = *reinterpret_cast<const EeQuad*>(hi + c - j - 3);
+        if (pair) {
+          q[i][2] = *reinterpret_cast<const EeQuad*>(lo + c + j);
+          q[i][3] = *reinterpret_cast<const EeQuad*>(lo + c - j - 3);
+        }
+      }
+    }
+    // radius window of this row distance
+    const double rem = r2 - (double)dv * (double)dv;
+    const int w = rem >= 0.0 ? isqrt_floor(rem) : -1;
+    // pixels outside the folded part, with the windows that reach them (few; uniform addresses)
+    double edge = 0.0, edge_tot = 0.0;
+    auto single = [&](int u) {
+      double v = (double)hi[u];
+      if (pair) v += (double)lo[u];
+      edge_tot += v;
+      if (abs(u - c) <= w) edge += v;
+    };
+    for (int u = c + H; u < M; ++u) single(u);
+    for (int u = c - (H > 0 ? H : 1); u >= 0; --u) single(u);
+    double carry = 0.0;
+#pragma unroll
+    for (int i = 0; i < STEPS; ++i) {
+      double p[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        // the centre column (j = 0) has no mirror image
+        const bool centre = i == 0 && k == 0 && lane == 0;
+        double t = (double)q[i][0][k] + (double)q[i][2][k];
+        const double f = (double)q[i][1][3 - k] + (double)q[i][3][3 - k];
+        t += centre ? 0.0 : f;
+        p[k] = k > 0 ? p[k - 1] + t : t;
+      }
+      const double inc = ee_scan(p[3], lane);
+      const double base = carry + (inc - p[3]);
+      const int j = 256 * i + 4 * lane;
+      if (j < H) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) pre[j + k] = base + p[k];
+      }
+      carry += __shfl(inc, 63);
+    }
+    // the prefixes are written and read by this wavefront only: order its LDS accesses
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    tot += carry + edge_tot;
+    if (w >= 0) acc += (H > 0 ? pre[min(w, H - 1)] : 0.0) + edge;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+  if (lane < a.n_r) fin[wave][lane] = acc;
+  if (lane == 0) fin[wave][a.n_r] = tot;
   __syncthreads();
   if ((int)threadIdx.x <= a.n_r) {
     double t = 0.0;
-    for (int w = 0; w < nw; ++w) t += reinterpret_cast<const double*>(ee_smem + (size_t)w * ee_wave_lds(M))[threadIdx.x];
-    a.ws[((int64_t)s * kEeGroups + g) * (a.n_r + 1) + threadIdx.x] = t;
+#pragma unroll
+    for (int v = 0; v < kEeWaves; ++v) t += fin[v][threadIdx.x];
+    a.ws[((int64_t)s * (a.n_r + 1) + threadIdx.x) * kEeGroups + g] = t;
   }
 }
 
 // Pass 2: block s adds the groups of PSF s and divides by the total.  Wavefront w takes entries
-// k = w, w + 4, ... <= n_r; lane l adds groups l, l + 64, ... in order, then a fixed tree over
+// k = w, w + 16, ... <= n_r; lane l adds groups l, l + 64, ... (read together), then a fixed tree over
 // the lanes.
-__global__ __launch_bounds__(256) void ee_final_kernel(const EeLaunch a) {
+constexpr int kEeFinalWaves = 16;
+__global__ __launch_bounds__(64 * kEeFinalWaves) void ee_final_kernel(const EeLaunch a) {
   __shared__ double s_tot[kMaxRadii + 1];
   const int s = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const double* w = a.ws + (int64_t)s * kEeGroups * (a.n_r + 1);
-  for (int k = wave; k <= a.n_r; k += 4) {
+  constexpr int kParts = (kEeGroups + 63) / 64;
+  for (int k = wave; k <= a.n_r; k += kEeFinalWaves) {
+    const double* w = a.ws + ((int64_t)s * (a.n_r + 1) + k) * kEeGroups;
+    double v[kParts];
+#pragma unroll
+    for (int t = 0; t < kParts; ++t) v[t] = lane + 64 * t < kEeGroups ? w[lane + 64 * t] : 0.0;
     double x = 0.0;
-    for (int gi = lane; gi < kEeGroups; gi += 64) x += w[gi * (a.n_r + 1) + k];
+#pragma unroll
+    for (int t = 0; t < kParts; ++t) x += v[t];
     for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
     if (lane == 0) s_tot[k] = x;
   }
@@ -147,10 +168,17 @@ __global__ __launch_bounds__(256) void ee_final_kernel(const EeLaunch a) {
 }
 
 hipError_t launch_encircled_energy(const EeLaunch& a, hipStream_t st) {
-  // 4 wavefronts per block when their LDS fits in 64 KB (M <= 3100 or so), else 2 (M <= 4096)
-  const int nw = 4 * ee_wave_lds(a.m) <= 65536 ? 4 : 2;
-  hipLaunchKernelGGL(ee_rows_kernel, dim3(kEeGroups, (unsigned)a.n_psf), dim3(64 * nw), nw * ee_wave_lds(a.m), st, a);
-  hipLaunchKernelGGL(ee_final_kernel, dim3((unsigned)a.n_psf), dim3(256), 0, st, a);
+  const int c = a.m / 2;
+  const int h = (a.m - c < c + 1 ? a.m - c : c + 1) & ~3;
+  const size_t lds = (size_t)kEeWaves * h * sizeof(double);
+  const dim3 grid(kEeGroups, (unsigned)a.n_psf);
+  if (h <= 4 * 256)
+    hipLaunchKernelGGL(ee_rows_kernel<4>, grid, dim3(64 * kEeWaves), lds, st, a);
+  else if (h <= kEeSteps * 256)
+    hipLaunchKernelGGL(ee_rows_kernel<kEeSteps>, grid, dim3(64 * kEeWaves), lds, st, a);
+  else
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(ee_final_kernel, dim3((unsigned)a.n_psf), dim3(64 * kEeFinalWaves), 0, st, a);
   return hipGetLastError();
 }
 

@@ -552,6 +552,21 @@ int shw_push_pull(const float* d_slopes, int32_t n_modes, int32_t n_slopes, floa
                   void* hip_stream);
 
 /*
+ * shw_wfs_interaction_matrix: the interaction matrix of n_modes actuators (host array acts) without
+ * their frames: what shw_dm_influence_opd with +-amplitude_m (FP32), sh_wfs_measure of every sensor on
+ * each frame and shw_push_pull with `scale` give, computed only in the sub-apertures that a mode's
+ * patch reaches; every other entry is 0 (there push and pull see the same flat wavefront), and so is
+ * the column of an actuator index outside [0, n_act).  d_im[s * ld_im + m], s < n_wfs * 2 * n_valid,
+ * m < n_modes.  (row0, col0): the pupil's window of the surface, SHW_E_INVALID if it leaves it.
+ * SHW_E_UNSUPPORTED, with nothing launched, for plans with noise, sodium sub-layers or a precision
+ * form, shapes other than 10-pixel sub-apertures with fft_n = conv_n = 40 and det_n = 16, launch
+ * variants other than 13, and patches that reach across the whole pupil.  Asynchronous.
+ */
+int shw_wfs_interaction_matrix(shw_wfs_plan* plan, const shw_dm_plan* dm, const int32_t* acts, int32_t n_modes,
+                               float amplitude_m, int32_t row0, int32_t col0, float scale, float* d_im,
+                               int64_t ld_im, void* hip_stream);
+
+/*
  * Residual OPD of n_out pupils: out_k[y][x] = screen[sr_k + y][sc_k + x]
  * - sum_d surf_d[r_kd + y][c_kd + x] for y, x < pupil_n, where (sr_k, sc_k)
  * and (r_kd, c_kd) are window origins (rows, columns) given per output k

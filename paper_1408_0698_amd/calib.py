@@ -23,8 +23,12 @@ def interaction_matrix(plan: "shwfs.WfsPlan", dm: "shwfs.DmPlan", acts, amplitud
     N = plan.cfg.pupil_n
     n_slopes = plan.n_wfs * 2 * plan.n_valid
     im = torch.empty((n_slopes, n_modes), device="cuda")
-    acts = np.asarray(acts, dtype=np.int32)
-    for m0 in range(0, n_modes, chunk):
+    acts = np.ascontiguousarray(acts, dtype=np.int32)
+    chunks = range(0, n_modes, chunk)
+    if n_modes and shwfs.interaction_matrix(plan, dm, acts, amplitude_m, row0, col0, 1.0 / (2.0 * amplitude_m), im,
+                                            stream=stream):
+        return im
+    for m0 in chunks:
         n = min(chunk, n_modes - m0)
         act = torch.from_numpy(np.repeat(acts[m0:m0 + n], 2)).cuda()
         amp = torch.from_numpy(np.tile(np.array([amplitude_m, -amplitude_m], np.float32), n)).cuda()

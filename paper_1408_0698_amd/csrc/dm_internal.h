@@ -55,6 +55,8 @@ hipError_t launch_influence_opd(const InfluenceLaunch& a, float* out, hipStream_
 // im[s * ld + m] = (slopes[2m][s] - slopes[2m+1][s]) * scale for m < n_modes, s < n_slopes.
 hipError_t launch_push_pull(const float* slopes, int32_t n_modes, int32_t n_slopes, float scale, float* im,
                             int64_t ld, hipStream_t st);
+// im[r * ld + c] = v for r < rows, c < cols.
+hipError_t launch_fill_matrix(float* im, int64_t rows, int32_t cols, int64_t ld, float v, hipStream_t st);
 hipError_t launch_residual(ResidualLaunch& a, int n_dm, float* out, hipStream_t st);
 
 }  // namespace shw

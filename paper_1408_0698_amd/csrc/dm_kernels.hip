@@ -217,7 +217,29 @@ __global__ __launch_bounds__(256) void push_pull_kernel(const float* __restrict_
   }
 }
 
+// Four elements of a row per thread.
+__global__ __launch_bounds__(256) void fill_matrix_kernel(float* __restrict__ im, int64_t quads, int32_t row_quads,
+                                                           int32_t cols, int64_t ld, float v) {
+  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (e >= quads) return;
+  const int64_t r = e / row_quads;
+  const int32_t c = 4 * (int32_t)(e - r * row_quads);
+  float* p = im + r * ld + c;
+  if (c + 4 <= cols) {
+    *reinterpret_cast<QuadV*>(p) = QuadV{v, v, v, v};
+  } else {
+    for (int k = 0; c + k < cols; ++k) p[k] = v;
+  }
+}
+
 }  // namespace
+
+hipError_t launch_fill_matrix(float* im, int64_t rows, int32_t cols, int64_t ld, float v, hipStream_t st) {
+  const int32_t rq = (cols + 3) / 4;
+  const int64_t quads = rows * rq;
+  hipLaunchKernelGGL(fill_matrix_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, st, im, quads, rq, cols, ld, v);
+  return hipGetLastError();
+}
 
 hipError_t launch_influence_opd(const InfluenceLaunch& a, float* out, hipStream_t st) {
   if (a.n <= 0) return hipSuccess;

@@ -58,6 +58,21 @@ struct WfsLaunch {
   int64_t item0;
 };
 
+// One launch of push-pull calibration pairs: the modes' influence functions (one patch of pixels each)
+// reach nb x nb sub-apertures at most; a pair is one mode, sensor and cell of that box.
+constexpr int kModesChunk = 800;  // modes per launch (their actuators travel in the arguments)
+struct ModesLaunch {
+  WfsLaunch a;               // tables and geometry of the sensors; total = 2 x pairs
+  const float* act_xy;       // actuator (x, y) in pixels from the mirror's centre
+  const int32_t* inv;        // [n_subap^2] number of the valid sub-aperture, -1 elsewhere
+  float* im;                 // slope s of mode m at im[s * ld + m]
+  int64_t ld;
+  int32_t n_modes, n_act, half, half_patch, row0, col0, npx, nb, shift, pad0;
+  uint32_t dm_mode_m, dm_mode_s, dm_cell_m, dm_cell_s, dm_nb_m, dm_nb_s;  // by n_wfs nb^2, nb^2 and nb
+  float amp, inv_2s2, scale, pad1;
+  int32_t act[kModesChunk];
+};
+
 // Multiplier m and shift s for unsigned division by an invariant d (1 <= d < 2^31) of dividends
 // n < 2^31: with l = ceil(log2 d) and m = floor(2^32 (2^l - d) / d) + 1, floor(n / d) =
 // (umulhi(n, m) + n) >> l (Granlund and Montgomery, "Division by invariant integers using
@@ -93,6 +108,10 @@ bool wfs_variant_needs_det_ws(const WfsShape& s, int variant);
 
 // Launch the fused kernel for a.total work items. Returns the HIP error.
 hipError_t launch_wfs_fused(const WfsShape& s, int variant, const WfsLaunch& a, hipStream_t st);
+
+// Calibration pairs of a shape with plan variant `variant` (noise off).
+bool wfs_modes_supported(const WfsShape& s, int variant);
+hipError_t launch_wfs_modes(const WfsShape& s, const ModesLaunch& q, hipStream_t st);
 
 // *d_counter += inc (one lane).
 hipError_t launch_counter_add(uint64_t* d_counter, uint64_t inc, hipStream_t st);

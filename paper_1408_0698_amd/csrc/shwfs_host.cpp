@@ -65,6 +65,7 @@ struct shw_wfs_plan {
   WfsShape shape{};
   int device = 0;
   int32_t* d_valid = nullptr;
+  int32_t* d_inv = nullptr;      // shapes with calibration pairs: number of each valid sub-aperture, in d_valid's block
   float* d_khat = nullptr;
   float* d_khat_band = nullptr;  // in-band K^ rows of the band-limited variants, or null
   size_t bytes = 0;
@@ -440,14 +441,20 @@ static int plan_create(const shw_wfs_config* cfg, int32_t n_wfs, const shw_lgs_g
     delete p;
     return hip_fail(e, "hipGetDevice");
   }
-  e = hipMalloc(&p->d_valid, sizeof(int32_t) * p->n_valid);
-  if (e == hipSuccess)
-    e = hipMemcpy(p->d_valid, p->valid.data(), sizeof(int32_t) * p->n_valid, hipMemcpyHostToDevice);
+  // the valid table, then (shapes with calibration pairs) its inverse: -1 for the other sub-apertures
+  std::vector<int32_t> tab = p->valid;
+  if (wfs_shape_supported(p->shape) && wfs_modes_supported(p->shape, wfs_default_variant(p->shape))) {
+    tab.resize((size_t)p->n_valid + (size_t)cfg->n_subap * cfg->n_subap, -1);
+    for (int32_t i = 0; i < p->n_valid; ++i) tab[(size_t)p->n_valid + p->valid[i]] = i;
+  }
+  e = hipMalloc(&p->d_valid, sizeof(int32_t) * tab.size());
+  if (e == hipSuccess) e = hipMemcpy(p->d_valid, tab.data(), sizeof(int32_t) * tab.size(), hipMemcpyHostToDevice);
   if (e != hipSuccess) {
     shw_wfs_plan_destroy(p);
     return hip_fail(e, "plan tables");
   }
-  p->bytes = sizeof(int32_t) * p->n_valid;
+  if (tab.size() > (size_t)p->n_valid) p->d_inv = p->d_valid + p->n_valid;
+  p->bytes = sizeof(int32_t) * tab.size();
   if (n_sub > 0) {
     e = hipMalloc(&p->d_sub, sizeof(double) * sub_tab.size());
     if (e == hipSuccess)
@@ -1350,6 +1357,61 @@ extern "C" int shw_dm_influence_opd(const shw_dm_plan* p, const int32_t* d_act, 
   a.out_stride = out_stride;
   hipError_t e = launch_influence_opd(a, d_out, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "shw_dm_influence_opd launch");
+  return ok();
+}
+
+extern "C" int shw_wfs_interaction_matrix(shw_wfs_plan* p, const shw_dm_plan* dm, const int32_t* acts, int32_t n_modes,
+                                          float amplitude_m, int32_t row0, int32_t col0, float scale, float* d_im,
+                                          int64_t ld_im, void* stream) {
+  if (!p || !dm) return fail(SHW_E_INVALID, "plan is NULL");
+  if (n_modes < 0) return fail(SHW_E_INVALID, "n_modes %d < 0", n_modes);
+  if (n_modes == 0) return ok();
+  if (!acts || !d_im) return fail(SHW_E_INVALID, "NULL argument");
+  const int32_t n = p->cfg.pupil_n;
+  if (row0 < 0 || col0 < 0 || row0 + (int64_t)n > dm->size || col0 + (int64_t)n > dm->size)
+    return fail(SHW_E_INVALID, "pupil window (%d, %d) + %d leaves the %d-pixel surface", row0, col0, n, dm->size);
+  if (ld_im < n_modes) return fail(SHW_E_INVALID, "ld_im %lld < n_modes %d", (long long)ld_im, n_modes);
+  // noise is drawn for every sub-aperture of every frame, so only noise-free pushes leave the
+  // untouched ones exactly alike
+  if ((p->cfg.flags & SHW_FLAG_NOISE) || p->prec != SHW_PREC_FP32 || p->big || !p->d_inv ||
+      !wfs_modes_supported(p->shape, p->variant))
+    return fail(SHW_E_UNSUPPORTED, "no calibration kernel for this plan and launch variant");
+  const int32_t nb = (dm->patch - 1) / p->npx + 2;
+  const int64_t per_mode = (int64_t)p->n_wfs * nb * nb;
+  if (nb >= p->cfg.n_subap || per_mode >= ((int64_t)1 << 30))
+    return fail(SHW_E_UNSUPPORTED, "an influence function reaches the whole pupil");
+  ModesLaunch q{};
+  q.a = base_launch(p);
+  q.act_xy = dm->d_act_xy;
+  q.inv = p->d_inv;
+  q.ld = ld_im;
+  q.n_act = dm->n_act;
+  q.half = dm->size / 2;
+  q.half_patch = dm->patch / 2;
+  q.row0 = row0;
+  q.col0 = col0;
+  q.npx = p->npx;
+  q.nb = nb;
+  q.shift = (dm->size + dm->patch) / p->npx + 1;
+  div_magic((uint32_t)per_mode, &q.dm_mode_m, &q.dm_mode_s);
+  div_magic((uint32_t)(nb * nb), &q.dm_cell_m, &q.dm_cell_s);
+  div_magic((uint32_t)nb, &q.dm_nb_m, &q.dm_nb_s);
+  q.amp = amplitude_m;
+  q.inv_2s2 = (float)(1.0 / (2.0 * dm->sigma * dm->sigma));
+  q.scale = scale;
+  hipStream_t st = (hipStream_t)stream;
+  // the difference of equal slopes times the scale (0 for any finite scale)
+  hipError_t e = launch_fill_matrix(d_im, (int64_t)p->n_wfs * 2 * p->n_valid, n_modes, ld_im, 0.0f * scale, st);
+  const int64_t fit = (((int64_t)1 << 31) - 8) / per_mode;  // pair numbers stay below 2^31
+  const int32_t chunk = fit < kModesChunk ? (int32_t)fit : kModesChunk;
+  for (int32_t m0 = 0; m0 < n_modes && e == hipSuccess; m0 += chunk) {
+    q.n_modes = n_modes - m0 < chunk ? n_modes - m0 : chunk;
+    q.a.total = 2 * (int64_t)q.n_modes * per_mode;
+    std::copy(acts + m0, acts + m0 + q.n_modes, q.act);
+    q.im = d_im + m0;
+    e = launch_wfs_modes(p->shape, q, st);
+  }
+  if (e != hipSuccess) return hip_fail(e, "shw_wfs_interaction_matrix launch");
   return ok();
 }
 

@@ -178,11 +178,16 @@ __device__ __forceinline__ ItemRef resolve_item(const WfsLaunch& a, int64_t it, 
 // pixels l, l + 64, ...  q_pix [NPIX] and q_val [3][NPIX] are the wavefront's own queue arrays in
 // LDS.  The per-pixel noise is keyed by pixel, sub-aperture and frame (reading O8), so every
 // caller gives the same images; the centroid sums are FP32 (per lane, then a tree over the lanes)
-// instead of FP64, which moves a slope by a few 1e-5 detector pixels at most.
+// instead of FP64, which moves a slope by a few 1e-5 detector pixels at most.  Returns the slopes (0 and
+// empty when nothing is left above the threshold), the same in every lane.
+struct Centroid {
+  float x, y;
+  bool empty;
+};
+
 template <int DET_N, int HEAD>
-__device__ __forceinline__ void noise_image(const WfsLaunch& a, const ItemRef& ref, int64_t item,
-                                            const float* __restrict__ det, int lane, int* __restrict__ q_pix,
-                                            float* __restrict__ q_val) {
+__device__ __forceinline__ Centroid noise_image(const WfsLaunch& a, const ItemRef& ref, const float* __restrict__ det,
+                                                int lane, int* __restrict__ q_pix, float* __restrict__ q_val) {
   constexpr int NPIX = DET_N * DET_N;
   constexpr float CD = 0.5f * (float)(DET_N - 1);
   const uint32_t gsub = (uint32_t)(ref.w * a.n_valid + ref.i);
@@ -308,13 +313,54 @@ __device__ __forceinline__ void noise_image(const WfsLaunch& a, const ItemRef& r
   s0 = wave_sum_tree(s0);
   sx = wave_sum_tree(sx);
   sy = wave_sum_tree(sy);
+  const bool empty = !(s0 > 0.0f);
+  const float r = __builtin_amdgcn_rcpf(s0);
+  return Centroid{empty ? 0.0f : sx * r, empty ? 0.0f : sy * r, empty};
+}
+
+// Slopes and flag of one item to the call's buffers.
+__device__ __forceinline__ void store_centroid(const WfsLaunch& a, const ItemRef& ref, int64_t item, const Centroid& c,
+                                               int lane) {
   if (lane == 0) {
-    const bool empty = !(s0 > 0.0f);
-    const float r = __builtin_amdgcn_rcpf(s0);
-    ref.slopes_fw[ref.i] = empty ? 0.0f : sx * r;
-    ref.slopes_fw[a.n_valid + ref.i] = empty ? 0.0f : sy * r;
-    if (a.flags && !a.list) a.flags[item] = empty ? 1 : 0;
+    ref.slopes_fw[ref.i] = c.x;
+    ref.slopes_fw[a.n_valid + ref.i] = c.y;
+    if (a.flags && !a.list) a.flags[item] = c.empty ? 1 : 0;
   }
+}
+
+// Push-pull calibration items: pair p is one mode, sensor and sub-aperture of the box that the mode's
+// patch can reach (nb x nb sub-apertures from the one that holds the patch's first pixel).
+struct ModeRef {
+  bool active;      // a valid sub-aperture that the patch of an actuator of the mirror reaches
+  int m, w, i, sa, sb;
+  float ax, ay;     // actuator, pixels from the mirror's centre
+};
+
+__device__ __forceinline__ ModeRef resolve_mode(const ModesLaunch& q, uint32_t p) {
+  ModeRef r;
+  const uint32_t cells = (uint32_t)(q.nb * q.nb);
+  r.m = (int)udiv_magic(p, q.dm_mode_m, q.dm_mode_s);
+  uint32_t rem = p - (uint32_t)r.m * ((uint32_t)q.a.n_wfs * cells);
+  r.w = (int)udiv_magic(rem, q.dm_cell_m, q.dm_cell_s);
+  rem -= (uint32_t)r.w * cells;
+  const int cy = (int)udiv_magic(rem, q.dm_nb_m, q.dm_nb_s);
+  const int cx = (int)rem - cy * q.nb;
+  const int act = r.m < q.n_modes ? q.act[r.m] : -1;
+  const bool known = act >= 0 && act < q.n_act;
+  r.ax = known ? q.act_xy[2 * act] : 0.0f;
+  r.ay = known ? q.act_xy[2 * act + 1] : 0.0f;
+  // first pixel of the patch in the pupil (may lie outside), and the sub-aperture that holds it; the
+  // shift keeps the dividend of the division below positive
+  const int px = q.half + (int)r.ax - q.half_patch - q.col0, py = q.half + (int)r.ay - q.half_patch - q.row0;
+  const int b0 = (px + q.shift * q.npx) / q.npx - q.shift, a0 = (py + q.shift * q.npx) / q.npx - q.shift;
+  r.sa = a0 + cy;
+  r.sb = b0 + cx;
+  const bool reached = r.sa * q.npx < py + 2 * q.half_patch && r.sb * q.npx < px + 2 * q.half_patch;
+  const bool inside = r.sa >= 0 && r.sb >= 0 && r.sa < q.a.n_subap && r.sb < q.a.n_subap;
+  r.i = known && reached && inside ? q.inv[r.sa * q.a.n_subap + r.sb] : -1;
+  r.active = r.i >= 0;
+  if (!r.active) r.w = r.i = r.sa = r.sb = 0;
+  return r;
 }
 
 // LDS floats per item for the given shape.  Split row transforms keep N/2 spectrum rows (rows 0
@@ -337,11 +383,14 @@ struct FusedLayout {
 };
 
 // One group of SPB work items (one block's worth).  Every lane of the block calls it.
+// MODES: calibration items instead of the frames of the call: items 2p and 2p + 1 are the push and the
+// pull of pair p, their wavefront is computed here, and the pair's slope difference goes to the
+// interaction matrix.
 template <int NPX, int FFT_N, int CONV_N, int DET_N, bool LGS, int SPB, bool SPLIT, bool SUB, bool DSPLIT,
-          bool BL = false>
+          bool BL = false, bool MODES = false>
 __device__ __forceinline__ void wfs_fused_group(const WfsLaunch& a, int64_t group, uint32_t frame_base,
                                                 float* __restrict__ s_re, float* __restrict__ s_im, int tid,
-                                                const float2* __restrict__ qtw) {
+                                                const float2* __restrict__ qtw, const ModesLaunch* modes = nullptr) {
   constexpr int L = CONV_N;                  // lanes per item
   constexpr int R = FFT_N / NPX;             // column residues of the row pass
   constexpr int H = CONV_N / 2 + 1;          // stored half spectrum rows (kernel spectra)
@@ -363,14 +412,28 @@ __device__ __forceinline__ void wfs_fused_group(const WfsLaunch& a, int64_t grou
 
   const int s = tid / L;
   const int l = tid - s * L;
+  static_assert(!MODES || (BL && !DSPLIT && !SUB), "calibration items: band-limited path, centroid in the kernel");
   const int64_t item = a.item0 + group * SPB + s;
-  const bool active = item < a.total;
+  bool active = item < a.total;
   const int64_t it = active ? item : a.item0;
-  const ItemRef ref = resolve_item(a, it, frame_base, DET_N * DET_N);
+  ItemRef ref{};
+  ModeRef mode{};
+  int sa, sb;
+  if constexpr (MODES) {
+    mode = resolve_mode(*modes, (uint32_t)(group * (SPB / 2) + (s >> 1)));
+    active = mode.active;
+    if (!__syncthreads_or(active)) return;  // no item of the block is reached
+    ref.w = mode.w;
+    ref.i = mode.i;
+    sa = mode.sa;
+    sb = mode.sb;
+  } else {
+    ref = resolve_item(a, it, frame_base, DET_N * DET_N);
+    const int sidx = a.valid_idx[ref.i];
+    sa = (int)udiv_magic((uint32_t)sidx, a.dm_subap_m, a.dm_subap_s);
+    sb = sidx - sa * a.n_subap;
+  }
   const int w = ref.w, i = ref.i;
-  const int sidx = a.valid_idx[i];
-  const int sa = (int)udiv_magic((uint32_t)sidx, a.dm_subap_m, a.dm_subap_s);
-  const int sb = sidx - sa * a.n_subap;
   float* re = s_re + s * PLANE;
   float* im = s_im + s * PLANE;
   const float* opd_f = ref.opd_f;
@@ -421,8 +484,25 @@ __device__ __forceinline__ void wfs_fused_group(const WfsLaunch& a, int64_t grou
     using GlobalF = __attribute__((address_space(1))) const float;
     const GlobalF* gsrc = (const GlobalF*)src;
     float ov[NPX];
+    if constexpr (MODES) {
+      // influence function of the pair's actuator, pushed on even items and pulled on odd ones
+      const ModesLaunch& q = *modes;
+      const int pi = q.row0 + prow, pj = q.col0 + sb * NPX;  // mirror pixel of the row's first sample
+      const int cx = q.half + (int)mode.ax, cy = q.half + (int)mode.ay;
+      const float dy = (float)pi + 0.5f - (float)q.half - mode.ay;
+      const bool in_y = pi >= cy - q.half_patch && pi < cy + q.half_patch;
+      const float amp = (s & 1) ? -q.amp : q.amp;
 #pragma unroll
-    for (int x = 0; x < NPX; ++x) ov[x] = gsrc[x];
+      for (int x = 0; x < NPX; ++x) {
+        const int j = pj + x;
+        const float dx = (float)j + 0.5f - (float)q.half - mode.ax;
+        const bool in = in_y && j >= cx - q.half_patch && j < cx + q.half_patch;
+        ov[x] = in ? amp * expf(-(dx * dx + dy * dy) * q.inv_2s2) : 0.0f;
+      }
+    } else {
+#pragma unroll
+      for (int x = 0; x < NPX; ++x) ov[x] = gsrc[x];
+    }
     // pixel-centre x coordinates: ax0 + x is exact (half-integers far below 2^23)
     const float ax0 = (float)x0 + 0.5f - a.half_n;
     float2 z[NPX];
@@ -854,6 +934,22 @@ __device__ __forceinline__ void wfs_fused_group(const WfsLaunch& a, int64_t grou
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: item arithmetic on the scalar unit
     if (wave == NW - 1) return;
     float* qbase = wave < NW - 2 ? s_im + wave * QW : s_re + SPB * NPIX;
+    if constexpr (MODES) {
+      const ModeRef mr = resolve_mode(*modes, (uint32_t)(group * (SPB / 2) + wave));
+      if (!mr.active) return;
+      const int lane = tid & 63;
+      ItemRef r2{};
+      const Centroid push = noise_image<DET_N, 4>(a, r2, s_det + 2 * wave * NPIX, lane, reinterpret_cast<int*>(qbase),
+                                                  qbase + NPIX);
+      const Centroid pull = noise_image<DET_N, 4>(a, r2, s_det + (2 * wave + 1) * NPIX, lane,
+                                                  reinterpret_cast<int*>(qbase), qbase + NPIX);
+      if (lane < 2) {
+        const float d = lane == 0 ? push.x - pull.x : push.y - pull.y;
+        const int64_t slope = ((int64_t)mr.w * 2 + lane) * a.n_valid + mr.i;
+        modes->im[slope * modes->ld + mr.m] = d * modes->scale;
+      }
+      return;
+    }
     // unrolled: the rolled loop kept its uniform values live across both images and spilled
     // 25 scalar registers
 #pragma unroll
@@ -861,7 +957,9 @@ __device__ __forceinline__ void wfs_fused_group(const WfsLaunch& a, int64_t grou
       const int64_t it2 = a.item0 + group * SPB + si;
       if (it2 >= a.total) break;  // uniform over the wavefront
       const ItemRef r2 = resolve_item(a, it2, frame_base, NPIX);
-      noise_image<DET_N, 4>(a, r2, it2, s_det + si * NPIX, tid & 63, reinterpret_cast<int*>(qbase), qbase + NPIX);
+      const Centroid c2 =
+          noise_image<DET_N, 4>(a, r2, s_det + si * NPIX, tid & 63, reinterpret_cast<int*>(qbase), qbase + NPIX);
+      store_centroid(a, r2, it2, c2, tid & 63);
     }
     return;
   } else {
@@ -994,6 +1092,28 @@ __global__ __launch_bounds__(SPB * CONV_N) __attribute__((amdgpu_waves_per_eu(WP
   }
 }
 
+// Push-pull calibration with the code of launch variant 13 (noise off): one block per 4 pairs, the
+// wavefronts formed in the row pass, the slope differences written to the matrix.  Bound by VALU
+// issue like the frames: 256 modes of one 80 x 80 sensor (64 cells each, 16,384 pairs) take 70 us traced,
+// and the matrix's zeros 4 us; influence frames of the whole pupil, their measurement in all 4928
+// sub-apertures and the combination took 4.3 ms for the same bits.
+template <int NPX, int FFT_N, int CONV_N, int DET_N, int SPB, int WPE>
+__global__ __launch_bounds__(SPB * CONV_N) __attribute__((amdgpu_waves_per_eu(WPE))) void wfs_modes_kernel(
+    const ModesLaunch q) {
+  using LY = FusedLayout<NPX, FFT_N, CONV_N, DET_N, true, false, true>;
+  __shared__ __align__(16) float s_re[SPB * LY::PLANE];
+  __shared__ __align__(16) float s_im[SPB * LY::PLANE];
+  __shared__ float2 s_qtw[CONV_N];
+  constexpr TwiddleTable<CONV_N> tw{};
+  if ((int)threadIdx.x < CONV_N) {
+    const int k = threadIdx.x / (CONV_N / 4), c = threadIdx.x - k * (CONV_N / 4);
+    const int j = (k * c) % CONV_N;
+    s_qtw[threadIdx.x] = make_float2(tw.c[j], -tw.s[j]);
+  }
+  wfs_fused_group<NPX, FFT_N, CONV_N, DET_N, true, SPB, true, false, false, true, true>(
+      q.a, blockIdx.x, 0, s_re, s_im, (int)threadIdx.x, s_qtw, &q);
+}
+
 // Stage D of the detector-split variants: one wavefront per item over the detector values the
 // fused kernel left in det_ws (noise_image).
 template <int DET_N, int HEAD>
@@ -1008,7 +1128,8 @@ __global__ __launch_bounds__(256) void det_noise_kernel(const WfsLaunch a) {
   const int64_t item = a.item0 + (int64_t)blockIdx.x * 4 + wave;
   if (item >= a.total) return;  // whole wavefronts leave together; no block barrier below
   const ItemRef ref = resolve_item(a, item, frame_base, NPIX);
-  noise_image<DET_N, HEAD>(a, ref, item, a.det_ws + (item - a.item0) * NPIX, lane, q_pix[wave], q_val[wave]);
+  const Centroid c = noise_image<DET_N, HEAD>(a, ref, a.det_ws + (item - a.item0) * NPIX, lane, q_pix[wave], q_val[wave]);
+  store_centroid(a, ref, item, c, lane);
 }
 
 // Items per block: the smallest count whose lanes fill whole 64-wide waves, at least 256 lanes.
@@ -1214,6 +1335,20 @@ hipError_t launch_wfs_fused(const WfsShape& s, int variant, const WfsLaunch& a, 
   SHW_WFS_SHAPES(X)
 #undef X
   return hipErrorInvalidValue;
+}
+
+bool wfs_modes_supported(const WfsShape& s, int variant) {
+  return SHW_SHAPE_MATCH(10, 40, 40, 16, true, false) && variant == kTunedVariants + 2;
+}
+
+hipError_t launch_wfs_modes(const WfsShape& s, const ModesLaunch& q, hipStream_t st) {
+  if (!SHW_SHAPE_MATCH(10, 40, 40, 16, true, false)) return hipErrorInvalidValue;
+  constexpr int SPB = items_per_block(40);
+  const int64_t pairs = (int64_t)q.n_modes * q.a.n_wfs * q.nb * q.nb;
+  const int64_t blocks = (pairs + SPB / 2 - 1) / (SPB / 2);
+  if (blocks <= 0) return hipSuccess;
+  hipLaunchKernelGGL((wfs_modes_kernel<10, 40, 40, 16, SPB, 7>), dim3((unsigned)blocks), dim3(SPB * 40), 0, st, q);
+  return hipGetLastError();
 }
 
 __global__ void counter_add_kernel(uint64_t* c, uint64_t inc) {

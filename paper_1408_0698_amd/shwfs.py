@@ -100,6 +100,8 @@ _sig = {
     "shw_dm_influence_opd": (C.c_int, [_P, _P, _P, C.c_int32, C.c_int32, C.c_int32, C.c_int32, _P, C.c_int64,
                                        C.c_int64, _P]),
     "shw_push_pull": (C.c_int, [_P, C.c_int32, C.c_int32, C.c_float, _P, C.c_int64, _P]),
+    "shw_wfs_interaction_matrix": (C.c_int, [_P, _P, C.POINTER(C.c_int32), C.c_int32, C.c_float, C.c_int32, C.c_int32,
+                                             C.c_float, _P, C.c_int64, _P]),
     "shw_recon_plan_create": (C.c_int, [C.c_int32, C.c_int32, C.POINTER(_P)]),
     "shw_recon_step": (C.c_int, [_P, _P, C.c_int64, _P, C.c_float, _P, _P, _P]),
     "shw_recon_plan_destroy": (C.c_int, [_P]),
@@ -614,3 +616,15 @@ def push_pull(slopes, n_modes, scale, im, stream=None):
     _check(_lib.shw_push_pull(_ptr(slopes), n_modes, slopes.shape[-1], scale, _ptr(im), im.stride(0),
                               _stream_ptr(stream)), "shw_push_pull")
     return im
+
+
+def interaction_matrix(plan, dm, acts, amplitude_m, row0, col0, scale, im, stream=None):
+    """im[s, m] (row pitch im.stride(0)) = push-pull slopes of actuator acts[m] (contiguous int32 numpy array)
+    times scale, computed only where the mode reaches.  False, with nothing launched, if the library has
+    no kernel for this plan or refuses the arguments."""
+    rc = _lib.shw_wfs_interaction_matrix(plan._h, dm._h, acts.ctypes.data_as(C.POINTER(C.c_int32)), len(acts),
+                                         amplitude_m, row0, col0, scale, _ptr(im), im.stride(0), _stream_ptr(stream))
+    if rc in (E_UNSUPPORTED, E_INVALID):
+        return False
+    _check(rc, "shw_wfs_interaction_matrix")
+    return True

@@ -109,6 +109,11 @@ bool wfs_variant_needs_det_ws(const WfsShape& s, int variant);
 // Launch the fused kernel for a.total work items. Returns the HIP error.
 hipError_t launch_wfs_fused(const WfsShape& s, int variant, const WfsLaunch& a, hipStream_t st);
 
+// Noise-free, threshold-free measurement of small NGS sub-apertures (8 pixels, FFT 16): slopes from the
+// field's line moments, the image only when one is asked for (images: some item of the call wants it).
+bool wfs_moments_supported(const WfsShape& s, const WfsLaunch& a);
+hipError_t launch_wfs_moments(const WfsShape& s, const WfsLaunch& a, bool images, hipStream_t st);
+
 // Calibration pairs of a shape with plan variant `variant` (noise off).
 bool wfs_modes_supported(const WfsShape& s, int variant);
 hipError_t launch_wfs_modes(const WfsShape& s, const ModesLaunch& q, hipStream_t st);

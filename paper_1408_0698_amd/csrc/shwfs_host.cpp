@@ -645,6 +645,12 @@ static int launch_big_list(shw_wfs_plan* p, const WfsLaunch& a, void* stream) {
   return ok();
 }
 
+// The plan's FP32 kernels for the items of a (images: some item wants its detector image).
+static hipError_t launch_plan(const shw_wfs_plan* p, const WfsLaunch& a, bool images, hipStream_t st) {
+  if (wfs_moments_supported(p->shape, a)) return launch_wfs_moments(p->shape, a, images, st);
+  return launch_wfs_fused(p->shape, p->variant, a, st);
+}
+
 static int measure_impl(shw_wfs_plan* p, const float* d_opd_m, int64_t row_pitch, int64_t wfs_stride,
                         int64_t frame_stride, int32_t n_frames, uint64_t seed, uint64_t frame0,
                         const uint64_t* d_frame0, float* d_slopes, float* d_images, uint8_t* d_flags, void* stream,
@@ -678,7 +684,7 @@ static int measure_impl(shw_wfs_plan* p, const float* d_opd_m, int64_t row_pitch
     if (e != hipSuccess) return hip_fail(e, "sh_wfs_measure launch");
     return ok();
   }
-  hipError_t e = launch_wfs_fused(p->shape, p->variant, a, (hipStream_t)stream);
+  hipError_t e = launch_plan(p, a, d_images != nullptr, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "sh_wfs_measure launch");
   return ok();
 }
@@ -752,7 +758,9 @@ extern "C" int sh_wfs_measure_batch(const shw_work* items, int32_t n, void* stre
       const int rc = launch_big_list(p, a, stream);
       if (rc != SHW_OK) return rc;
     } else {
-      e = launch_wfs_fused(p->shape, p->variant, a, (hipStream_t)stream);
+      bool images = false;
+      for (const FrameWork& w : list) images = images || w.images != nullptr;
+      e = launch_plan(p, a, images, (hipStream_t)stream);
       if (e != hipSuccess) return hip_fail(e, "sh_wfs_measure_batch launch");
     }
   }

@@ -1132,6 +1132,212 @@ __global__ __launch_bounds__(256) void det_noise_kernel(const WfsLaunch a) {
   store_centroid(a, ref, item, c, lane);
 }
 
+// ---------------------------------------------------------------- small noise-free NGS sub-apertures
+// Without a sodium kernel, noise and threshold, the centre of gravity needs no image.  With W the
+// rebin weights, sum_p (p - CD) D[p][q] summed over q is a weighted sum of the spot's marginal, and
+// by Parseval the marginal over v of |F|^2 is that of the row transforms G_y(u) alone:
+//   sum_u c(u) sum_v |F(v,u)|^2 / N^2 = (1/N) sum_y sum_u c(u) |G_y(u)|^2,  c(u) = sum_p (p - CD) W[p][u].
+// The inner sum is a quadratic form in the row's NPX field values e(x); c is antisymmetric about
+// (N - 1)/2, so it is sum_{d>0} 2 S(d) sum_x Im(e(x + d) conj e(x)), S(d) = sum_u c(u) sin(2 pi (u - (N-1)/2) d / N).
+// The image's total is sum |e|^2.  The slopes thus take NPX (NPX - 1) / 2 products per row and per column of
+// the field instead of a two-dimensional transform.  The table holds 2 S(d) / N.
+template <int NPX, int N, int DN>
+struct MomentWeights {
+  double w[NPX];
+  constexpr MomentWeights() : w() {
+    const double b = (double)N / (double)DN;
+    for (int d = 0; d < NPX; ++d) {
+      double s = 0.0;
+      for (int u = 0; u < N; ++u) {
+        double c = 0.0;
+        for (int p = 0; p < DN; ++p) {
+          const double lo = (double)u > b * p ? (double)u : b * p;
+          const double hi = (double)(u + 1) < b * (p + 1) ? (double)(u + 1) : b * (p + 1);
+          if (hi > lo) c += (hi - lo) * ((double)p - 0.5 * (double)(DN - 1));
+        }
+        s += c * ct_sin_frac((long)(2 * u - N + 1) * d, 2 * N);
+      }
+      w[d] = 2.0 * s / (double)N;
+    }
+  }
+};
+
+// sum_{d>0} w[d] sum_x Im(e(x + d) conj e(x)) of one line of the field.
+template <int NPX, int N, int DN>
+__device__ __forceinline__ double line_moment(const float2 (&e)[NPX]) {
+  constexpr MomentWeights<NPX, N, DN> mw{};
+  double acc = 0.0;
+#pragma unroll
+  for (int d = 1; d < NPX; ++d) {
+    float t = 0.0f;
+#pragma unroll
+    for (int x = 0; x + d < NPX; ++x) {
+      t = fmaf(e[x + d].y, e[x].x, t);
+      t = fmaf(-e[x + d].x, e[x].y, t);
+    }
+    acc = fma(mw.w[d], (double)t, acc);
+  }
+  return acc;
+}
+
+// v + (v of the lanes reached by DPP control CTRL), FP64
+template <int CTRL>
+__device__ __forceinline__ double dpp_add_f64(double v) {
+  const int64_t b = __double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)b, CTRL, 0xF, 0xF, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, true);
+  return v + __longlong_as_double(((int64_t)hi << 32) | lo);
+}
+// Sum over each group of 8 lanes, in every lane: pairs, quads, then the two quads of the group
+// (a reversed half row pairs each lane with one of the other quad).
+__device__ __forceinline__ double sum8(double v) {
+  v = dpp_add_f64<0xB1>(v);   // quad_perm 1, 0, 3, 2
+  v = dpp_add_f64<0x4E>(v);   // quad_perm 2, 3, 0, 1
+  return dpp_add_f64<0x141>(v);  // row_half_mirror
+}
+
+// x exp(2 pi i j / M) for a compile-time angle
+template <int M>
+__device__ __forceinline__ float2 rotate(float2 x, int j) {
+  j %= M;
+  return twiddle_mul<M, 1>(x, j < 0 ? j + M : j);
+}
+
+// One 8-lane group per sub-aperture of 8 x 8 pixels (FFT 16), 8 of them per wavefront: lane y forms row y
+// of the field (every phase once) and its moment, the field goes through LDS within the wavefront, and lane
+// x takes column x.  The products of a lag are summed in FP32 (at most 14 terms), everything above in FP64.
+// IMG: the image too, from the pruned row and column transforms: lane l ends with detector column l (two
+// columns of 16-pixel detectors).  The slopes do not depend on whether the image is asked for.
+// Bound by HBM for many frames: 4096 frames of 80 sub-apertures (107 MB) without images take 26.7 us,
+// 4.0 TB/s; the two-dimensional transform on 16 lanes per sub-aperture, every phase formed twice and
+// the centroid added by one lane, took 84 us.  FP32 sums throughout would take 24.6 us (error against
+// 64 bits 1.0e-7 instead of 6.4e-8), FP64 products 30.4 us (6.3e-8).
+constexpr int kNgsWaves = 4;
+template <int DN, bool IMG>
+__global__ __launch_bounds__(64 * kNgsWaves) void wfs_ngs8_kernel(const WfsLaunch a) {
+  constexpr int NPX = 8, N = 16;
+  // row stride 9 and sub-aperture stride 72 complex values: the 16 lanes served together by an 8-byte
+  // access touch different bank pairs, by rows and by columns
+  constexpr int RS = 9, SS = 72;
+  __shared__ float2 s_f[kNgsWaves][8 * SS];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int y = lane & 7;
+  const int64_t item = a.item0 + ((int64_t)blockIdx.x * kNgsWaves + wave) * 8 + (lane >> 3);
+  const bool active = item < a.total;
+  const ItemRef ref = resolve_item(a, active ? item : a.item0, 0, DN * DN);
+  const int sidx = a.valid_idx[ref.i];
+  const int sa = (int)udiv_magic((uint32_t)sidx, a.dm_subap_m, a.dm_subap_s);
+  const int sb = sidx - sa * a.n_subap;
+  const int prow = sa * NPX + y;
+  // eight OPD samples of the row as two 16-byte reads at 4-byte alignment
+  typedef float Quad __attribute__((ext_vector_type(4), aligned(4)));
+  using GlobalQ = __attribute__((address_space(1))) const Quad;
+  const GlobalQ* src = (const GlobalQ*)(ref.opd_f + (int64_t)ref.w * ref.wfs_stride + (int64_t)prow * ref.row_pitch +
+                                        (int64_t)sb * NPX);
+  const Quad q0 = src[0], q1 = src[1];
+  const float ay = (float)prow + 0.5f - a.half_n;
+  const float ax0 = (float)(sb * NPX) + 0.5f - a.half_n;
+  float2 e[NPX];
+  float tot = 0.0f;
+#pragma unroll
+  for (int x = 0; x < NPX; ++x) {
+    const float ov = x < 4 ? q0[x & 3] : q1[x & 3];
+    const float ax = ax0 + (float)x;
+    const float r2 = ax * ax + ay * ay;
+    const float amp = r2 <= a.r2_outer && r2 >= a.r2_inner ? 1.0f : 0.0f;
+    // hardware sine and cosine take revolutions: exp(2 pi i OPD / lambda) after the FP64 reduction
+    const float fw = (float)__builtin_amdgcn_fract((double)ov * a.inv_lambda);
+    e[x] = make_float2(amp * __builtin_amdgcn_cosf(fw), amp * __builtin_amdgcn_sinf(fw));
+    tot = fmaf(e[x].x, e[x].x, tot);
+    tot = fmaf(e[x].y, e[x].y, tot);
+  }
+  float2* tile = s_f[wave] + (lane >> 3) * SS;
+#pragma unroll
+  for (int x = 0; x < NPX; ++x) tile[y * RS + x] = e[x];
+  const double mx = line_moment<NPX, N, DN>(e);
+  // the tile is written and read by this wavefront only: order its LDS accesses
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  float2 col[NPX];
+#pragma unroll
+  for (int k = 0; k < NPX; ++k) col[k] = tile[k * RS + y];
+  const double my = line_moment<NPX, N, DN>(col);
+  const double s0 = sum8((double)tot), sx = sum8(mx), sy = sum8(my);
+  if (active && y < 2) {
+    const bool empty = !(s0 > 0.0);
+    // the quotient by the hardware reciprocal, corrected by its remainder: rounded almost correctly
+    const float num = (float)(y == 0 ? sx : sy), den = (float)s0;
+    const float r = __builtin_amdgcn_rcpf(den);
+    const float v0 = num * r;
+    const float v = empty ? 0.0f : fmaf(fmaf(-den, v0, num), r, v0);
+    ref.slopes_fw[y * a.n_valid + ref.i] = v;
+    if (y == 0 && a.flags && !a.list) a.flags[item] = empty ? 1 : 0;
+  }
+  if constexpr (IMG) {
+    const float scale = (a.ph_scale > 0.0f ? a.ph_scale : 1.0f) / (float)(N * N);
+    float det[DN / 8][DN];  // this lane's detector columns
+#pragma unroll
+    for (int q = 0; q < DN / 8; ++q)
+#pragma unroll
+      for (int p = 0; p < DN; ++p) det[q][p] = 0.0f;
+#pragma unroll
+    for (int k2 = 0; k2 < 2; ++k2) {
+      // row transform, columns u = 2 k1 + k2: 8-point transforms of e(x) exp(2 pi i ((N-1)/2 - k2) x / N)
+      float2 z[NPX];
+#pragma unroll
+      for (int x = 0; x < NPX; ++x) z[x] = rotate<2 * N>(e[x], (N - 1 - 2 * k2) * x);
+      RegFFT<NPX, -1>::run(z);
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      __builtin_amdgcn_wave_barrier();  // the tile's previous contents have been read
+#pragma unroll
+      for (int k = 0; k < NPX; ++k) tile[y * RS + k] = z[k];
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      float2 g[NPX];  // column u = 2 lane + k2
+#pragma unroll
+      for (int k = 0; k < NPX; ++k) g[k] = tile[k * RS + y];
+#pragma unroll
+      for (int v2 = 0; v2 < 2; ++v2) {
+#pragma unroll
+        for (int k = 0; k < NPX; ++k) z[k] = rotate<2 * N>(g[k], (N - 1 - 2 * v2) * k);
+        RegFFT<NPX, -1>::run(z);
+#pragma unroll
+        for (int k = 0; k < NPX; ++k) {  // row v = 2 k + v2
+          float& d = DN == N ? det[k2 % (DN / 8)][(2 * k + v2) % DN] : det[0][k % DN];
+          d = fmaf(z[k].x, z[k].x, d);
+          d = fmaf(z[k].y, z[k].y, d);
+        }
+      }
+    }
+    if (active && ref.images_it) {
+#pragma unroll
+      for (int p = 0; p < DN; ++p)
+#pragma unroll
+        for (int q = 0; q < DN / 8; ++q) ref.images_it[p * DN + y * (DN / 8) + q] = det[q][p] * scale;
+    }
+  }
+}
+
+bool wfs_moments_supported(const WfsShape& s, const WfsLaunch& a) {
+  return s.npx == 8 && s.fft_n == 16 && s.conv_n == 16 && (s.det_n == 8 || s.det_n == 16) && s.lgs == 0 && s.sub == 0 &&
+         !a.noise && a.thr == 0.0f;
+}
+
+hipError_t launch_wfs_moments(const WfsShape& s, const WfsLaunch& a, bool images, hipStream_t st) {
+  const int64_t blocks = (a.total - a.item0 + 8 * kNgsWaves - 1) / (8 * kNgsWaves);
+  if (blocks <= 0) return hipSuccess;
+  const dim3 grid((unsigned)blocks), block(64 * kNgsWaves);
+  if (s.det_n == 8 && !images)
+    hipLaunchKernelGGL((wfs_ngs8_kernel<8, false>), grid, block, 0, st, a);
+  else if (s.det_n == 8)
+    hipLaunchKernelGGL((wfs_ngs8_kernel<8, true>), grid, block, 0, st, a);
+  else if (!images)
+    hipLaunchKernelGGL((wfs_ngs8_kernel<16, false>), grid, block, 0, st, a);
+  else
+    hipLaunchKernelGGL((wfs_ngs8_kernel<16, true>), grid, block, 0, st, a);
+  return hipGetLastError();
+}
+
 // Items per block: the smallest count whose lanes fill whole 64-wide waves, at least 256 lanes.
 constexpr int items_per_block(int lanes) {
   int spb = 1;

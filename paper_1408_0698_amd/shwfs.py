@@ -177,11 +177,30 @@ def geometry(cfg):
     return list(idx)[: n.value], list(il)[: n.value]
 
 
+def _raw_stream_call():
+    """(torch's handle of the current stream of a device, its current device), or None where this torch
+    has no such calls."""
+    import torch
+    c = torch._C
+    raw, device = getattr(c, "_cuda_getCurrentRawStream", None), getattr(c, "_cuda_getDevice", None)
+    return (raw, device, torch.cuda.is_initialized) if raw and device else None
+
+
+_raw_stream = None
+
+
 def _stream_ptr(stream):
-    if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+    """The given stream, or torch's current stream of the current device.  The handle is asked for directly:
+    torch.cuda.current_stream() builds a Stream object first, 2.7 us of an 8 us call."""
+    global _raw_stream
+    if stream is not None:
+        return C.c_void_p(stream.cuda_stream)
+    if _raw_stream is None:
+        _raw_stream = _raw_stream_call() or ()
+    if _raw_stream and _raw_stream[2]():
+        return C.c_void_p(_raw_stream[0](_raw_stream[1]()))
+    import torch
+    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
 def _ptr(t):
@@ -428,24 +447,34 @@ def polychromatic_psf(plans, weights, opd, out, strehl=None, stream=None):
     return out
 
 
+def _doubles(values):
+    """double C array of a list of numbers (array() copies a list several times faster than ctypes)."""
+    a = array("d", [float(v) for v in values] or [0.0])
+    return (C.c_double * len(a)).from_buffer(a)
+
+
 def _layer_args(layers):
     """layers: sequence of (screen float32 device [R][C] with unit column stride, spacing_m, altitude_m, x0, y0)."""
     n = len(layers)
-    ptrs = (C.c_void_p * n)(*[_ptr(l[0]) for l in layers])
-    rows = (C.c_int32 * n)(*[l[0].shape[0] for l in layers])
-    cols = (C.c_int32 * n)(*[l[0].shape[1] for l in layers])
-    pitch = (C.c_int64 * n)(*[l[0].stride(0) for l in layers])
+    ptrs, rows, cols, pitch, par = [], [], [], [], []
     for l in layers:
-        if l[0].dim() != 2 or l[0].stride(1) != 1:
+        scr = l[0]
+        shape, stride = scr.shape, scr.stride()
+        if len(shape) != 2 or stride[1] != 1:
             raise ValueError("screens must be [rows][cols] with unit column stride")
-    par = (C.c_double * (4 * n))(*[float(v) for l in layers for v in l[1:5]])
-    return n, ptrs, rows, cols, pitch, par
+        ptrs.append(scr.data_ptr())
+        rows.append(shape[0])
+        cols.append(shape[1])
+        pitch.append(stride[0])
+        par += l[1:5]
+    return (n, (C.c_void_p * n)(*ptrs), (C.c_int32 * n)(*rows), (C.c_int32 * n)(*cols), (C.c_int64 * n)(*pitch),
+            _doubles(par))
 
 
 def project_layers(layers, pupil_n, dx_m, targets, out, tilt=None, stream=None):
     """Cone-effect open-loop wavefronts: targets = [(theta_x, theta_y, altitude_m or 0)], out float32 [T][N][N]."""
     n, ptrs, rows, cols, pitch, par = _layer_args(layers)
-    tp = (C.c_double * (3 * max(1, len(targets))))(*[float(v) for t in targets for v in t])
+    tp = _doubles(chain.from_iterable(targets))
     if out.dim() != 3 or out.stride(2) != 1:
         raise ValueError("out must be [targets][rows][cols] with contiguous rows")
     _check(_lib.shw_project_layers(n, ptrs, rows, cols, pitch, par, pupil_n, dx_m, len(targets), tp, _ptr(tilt),
@@ -456,7 +485,7 @@ def project_layers(layers, pupil_n, dx_m, targets, out, tilt=None, stream=None):
 def uplink_tilt(layers, lgs, llt_diameter_m, n_samples, out, stream=None):
     """lgs = [(launch_x_m, launch_y_m, theta_x, theta_y, sodium_altitude_m)]; out float64 device [n][2] radians."""
     n, ptrs, rows, cols, pitch, par = _layer_args(layers)
-    lp = (C.c_double * (5 * max(1, len(lgs))))(*[float(v) for g in lgs for v in g])
+    lp = _doubles(chain.from_iterable(lgs))
     _check(_lib.shw_uplink_tilt(n, ptrs, rows, cols, pitch, par, len(lgs), lp, llt_diameter_m, n_samples, _ptr(out),
                                 _stream_ptr(stream)), "shw_uplink_tilt")
     return out

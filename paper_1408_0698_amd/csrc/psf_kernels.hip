@@ -21,19 +21,23 @@
 // values instead of 40, which keeps the kernels free of register spills.
 //
 // Row pass: 4 rows per block of 320 lanes; each lane of a pair computes half
-// of the row's phases (all its OPD loads issued first) and swaps them with its partner.  The intermediate is
-// stored in column blocks of 8: element (frame f, row y, column u) of T sits
-// at ((f * M/8 + u/8) * pupil_n + y) * 8 + u % 8, so that rows write whole
-// 64-byte runs and the 8 columns of a column block are one contiguous region.
-// Column pass: 4 columns per block; the 8 blocks of a 32-column group (one
-// 128-byte line of every accumulator row, and four column blocks of the
-// intermediate) are launched 8 apart, so the dispatcher places them on one
-// XCD and its L2 merges their reads of the intermediate and their writes of
-// the accumulator.  Frames are accumulated in LDS (each lane owns its 20
-// outputs, so no barrier), then one read-modify-write of the accumulator per
-// call, 16 bytes (the block's 4 columns) per row; the on-axis sample of each
-// frame is the Strehl ratio.  A 4-waves-per-
-// SIMD register target (128 VGPRs) lets 3 blocks share a CU.
+// of the row's phases (all its OPD loads issued first) and shares them with its partner.  The intermediate is
+// stored in column blocks of 4: element (frame f, row y, column u) of T sits
+// at ((f * M/4 + u/4) * pupil_n + y) * 4 + u % 4, and a wavefront holds 8 consecutive outputs of all four rows,
+// so that every store writes whole 128-byte lines (runs of 64 bytes, one row at a time, are written
+// at 3.4 TB/s on this card, whole lines at 5.8; the stores alone took 650 us of 9 x 20 star-frames).
+// Column pass: 4 columns per block, which are one contiguous region of T.  It is read straight into LDS, 16
+// bytes a lane, the next frame's while this one is transformed; the frames' sums stay in registers
+// (each lane owns its 20 outputs), then one read-modify-write of the accumulator per call, 16 bytes
+// (the block's 4 columns) per row, the 8 blocks of a 32-column group (one 128-byte line of every
+// accumulator row) launched 8 apart, so that the dispatcher places them on one XCD and its L2 merges
+// their writes; the on-axis sample of each frame is the Strehl ratio.  A 4-waves-per-
+// SIMD register target (128 VGPRs) lets 3 blocks share a CU; at 2 blocks (3 waves per SIMD, no spills) the pass
+// takes 1.17 instead of 0.88 ms.
+// 9 stars x 20 frames: 1.24 ms for both passes (traced: rows 0.56 ms, at 4.1 TB/s; columns 0.88 ms).  The rows are
+// bound by HBM; the columns by issue and the five barriers of a frame (with the reads taken out they took
+// 0.67 ms).  1.51 ms with T in column blocks of 8, one row or column per 80 consecutive lanes and each
+// lane reading its column with 64-byte strides.
 // Both passes have a form for pupil_n = M/2 (the Nyquist-sampled PSF), where
 // every sample of the pruned transforms lies in the pupil grid, so its loads
 // need no bounds masks.
@@ -51,39 +55,86 @@ constexpr int kQ = 40;            // M = kQ * kQ
 constexpr int kNZ = kM / 2 / kQ;  // non-zero n1 (20) = outputs per lane of the second step
 constexpr int kP = 2 * kQ;        // lanes per line
 constexpr int kLines = 4;         // lines per block
-constexpr int kST = kQ + 1;       // odd LDS stride
-constexpr int kCB = 8;            // columns per block of the intermediate
+// LDS plane of one line's transpose: element (row r, column n) at plane_at(r, n).  Lanes (q, h) write
+// (2k + h, q) and read (q, 2t + h); the 32 lanes served together (8 q, both h, two lines) touch 32 different
+// banks in both, because 84 = 20 mod 32 and the plane's size is 16 mod 32.
+constexpr int kPlane = (kQ / 2) * 84;
+// Sums of one line: output v = q + 40 (c + 20 h) at q + 40 c + kHalf h, lines kSumStride apart; 8 and 16
+// mod 32, for the same reason.
+constexpr int kHalf = kM / 2 + 8;
+constexpr int kSumStride = kM + 16;
+constexpr int kCB = kLines;       // columns per block of the intermediate
+constexpr int kFetch = kM / 2 * kLines * (int)sizeof(float2) / (16 * kLines * kP);  // 16-byte reads per lane and frame
+static_assert(kFetch * 16 * kLines * kP == kM / 2 * kLines * (int)sizeof(float2), "a frame's columns in whole reads");
+static_assert(kLines * kSumStride <= kLines * kPlane, "the sums fit the transposes' planes");
 constexpr int kGroupCols = 32;    // columns per 128-byte accumulator line (8 column-pass blocks)
 
 // Offset of element (star-frame sf, row y, column u) of the intermediate.
 __device__ __forceinline__ int64_t t_index(int64_t sf, int pupil_n, int y, int u) {
-  return ((sf * (kM / kCB) + (u >> 3)) * pupil_n + y) * kCB + (u & (kCB - 1));
+  return ((sf * (kM / kCB) + u / kCB) * pupil_n + y) * kCB + (u & (kCB - 1));
 }
 
-// Value of the same register in the partner lane t ^ 1 (DPP quad permutation 1, 0, 3, 2).
-__device__ __forceinline__ float pair_swap(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), 0xB1, 0xF, 0xF, false));
+// Values of the same register in other lanes of the pair: the partner's (DPP quad permutation
+// 1, 0, 3, 2), the even lane's (0, 0, 2, 2) and the odd lane's (1, 1, 3, 3).
+template <int CTRL>
+__device__ __forceinline__ float2 pair_perm(float2 v) {
+  return make_float2(__int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v.x), CTRL, 0xF, 0xF, true)),
+                     __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v.y), CTRL, 0xF, 0xF, true)));
 }
-__device__ __forceinline__ float2 pair_swap(float2 v) { return make_float2(pair_swap(v.x), pair_swap(v.y)); }
+__device__ __forceinline__ float2 pair_swap(float2 v) { return pair_perm<0xB1>(v); }
+__device__ __forceinline__ float2 pair_even(float2 v) { return pair_perm<0xA0>(v); }
+__device__ __forceinline__ float2 pair_odd(float2 v) { return pair_perm<0xF5>(v); }
+__device__ __forceinline__ int plane_at(int r, int n) { return (r >> 1) * 84 + (r & 1) * 2 + (n >> 1) * 4 + (n & 1); }
+
+// Lane pair and line of a thread: a wavefront holds 8 consecutive q of all four lines, so that the 4 x 8
+// values it moves at a time to or from the intermediate are whole 128-byte lines.
+__device__ __forceinline__ void lane_place(int tid, int& q, int& h, int& line) {
+  h = tid & 1;
+  q = ((tid >> 6) << 3) | ((tid >> 1) & 7);
+  line = (tid >> 4) & 3;
+}
+
+// Four-step twiddles W_M^(n2 k1) of lane (n2 = q, h), k1 = 2k + h: exact every 4 steps, products of
+// W_M^(2 n2) between.
+struct LineTwiddles {
+  float2 start[kNZ / 4], step;
+};
+__device__ __forceinline__ LineTwiddles line_twiddles(int q, int h) {
+  LineTwiddles tw;
+  constexpr float kInvM = 1.0f / (float)kM;
+  const float sr = -(float)(2 * q) * kInvM;  // 2 q < M
+  tw.step = make_float2(__builtin_amdgcn_cosf(sr), __builtin_amdgcn_sinf(sr));
+#pragma unroll
+  for (int b = 0; b < kNZ / 4; ++b) {
+    const float rev = -(float)(q * (8 * b + h)) * kInvM;  // q (8 b + h) < M
+    tw.start[b] = make_float2(__builtin_amdgcn_cosf(rev), __builtin_amdgcn_sinf(rev));
+  }
+  return tw;
+}
 
 // One M-point transform of a line with at most M/2 non-zero inputs v[n1] (sample 40 n1 + q),
 // on lane pair (q, h) of the line; pl is the line's LDS plane.  On return lane (q, h) holds
 // X[q + 40 (c + 20 h)] in x[c], c < 20.  Every lane of the block must call it.
-__device__ __forceinline__ void line_transform(const float2 (&v)[kNZ], float2 (&x)[kNZ], float* pl, int q, int h) {
+// `staged` runs once every lane of the block has the values it needed for v.
+template <class F>
+__device__ __forceinline__ void line_transform(const float2 (&v)[kNZ], float2 (&x)[kNZ], float* pl,
+                                               const LineTwiddles& tw, int q, int h, F staged) {
   float2 z[kNZ];
 #pragma unroll
-  for (int n1 = 0; n1 < kNZ; ++n1) z[n1] = h ? twiddle_mul<kQ, -1>(v[n1], n1) : v[n1];
+  for (int n1 = 0; n1 < kNZ; ++n1) z[n1] = v[n1];
+  if (h) {  // lanes with odd outputs
+#pragma unroll
+    for (int n1 = 0; n1 < kNZ; ++n1) z[n1] = twiddle_mul<kQ, -1>(z[n1], n1);
+  }
   RegFFT<kNZ, -1>::run(z);
-  // four-step twiddle W_M^(n2 k1), k1 = 2k + h: exact every 4 steps, products of W_M^(2 n2) between
+  // four-step twiddle W_M^(n2 k1), k1 = 2k + h
   {
-    const int n2 = q;
-    constexpr float kInvM = 1.0f / (float)kM;
-    const float sr = -(float)(2 * n2) * kInvM;  // 2 n2 < M
-    const float2 step = make_float2(__builtin_amdgcn_cosf(sr), __builtin_amdgcn_sinf(sr));
+    float2 step = tw.step;
+    // an opaque copy: in a loop over frames the products below are formed again rather than kept live
+    asm volatile("" : "+v"(step.x), "+v"(step.y));
 #pragma unroll
     for (int b = 0; b < kNZ / 4; ++b) {
-      const float rev = -(float)(n2 * (8 * b + h)) * kInvM;  // n2 (8 b + h) < M
-      float2 t = make_float2(__builtin_amdgcn_cosf(rev), __builtin_amdgcn_sinf(rev));
+      float2 t = tw.start[b];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         z[4 * b + e] = cmul(z[4 * b + e], t);
@@ -92,28 +143,33 @@ __device__ __forceinline__ void line_transform(const float2 (&v)[kNZ], float2 (&
     }
   }
   // transpose: lane (n2, h) holds Y[2k + h]; lane (k1, h) takes samples n2 = 2t + h
+  float* wr = pl + plane_at(h, q);   // row 2k + h is 84 k further on
+  const float* rd = pl + plane_at(q, h);  // column 2t + h is 4 t further on
 #pragma unroll
-  for (int k = 0; k < kNZ; ++k) pl[(2 * k + h) * kST + q] = z[k].x;
+  for (int k = 0; k < kNZ; ++k) wr[84 * k] = z[k].x;
+  __syncthreads();
+  staged();
+#pragma unroll
+  for (int t = 0; t < kNZ; ++t) x[t].x = rd[4 * t];
   __syncthreads();
 #pragma unroll
-  for (int t = 0; t < kNZ; ++t) x[t].x = pl[q * kST + 2 * t + h];
+  for (int k = 0; k < kNZ; ++k) wr[84 * k] = z[k].y;
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < kNZ; ++k) pl[(2 * k + h) * kST + q] = z[k].y;
-  __syncthreads();
-#pragma unroll
-  for (int t = 0; t < kNZ; ++t) x[t].y = pl[q * kST + 2 * t + h];
+  for (int t = 0; t < kNZ; ++t) x[t].y = rd[4 * t];
   __syncthreads();
   RegFFT<kNZ, -1>::run(x);
   if (h) {
 #pragma unroll
     for (int c = 0; c < kNZ; ++c) x[c] = twiddle_mul<kQ, -1>(x[c], c);
   }
+  // h = 0: X[c] = E + W O (partner holds W O); h = 1: X[c + 20] = E (partner) - W O, one fused operation
+  // by the lane's sign for both
+  const float sgn = h ? -1.0f : 1.0f;
 #pragma unroll
   for (int c = 0; c < kNZ; ++c) {
     const float2 o = pair_swap(x[c]);
-    // h = 0: X[c] = E + W O (partner holds W O); h = 1: X[c + 20] = E (partner) - W O
-    x[c] = h ? csub(o, x[c]) : cadd(x[c], o);
+    x[c] = make_float2(fmaf(sgn, x[c].x, o.x), fmaf(sgn, x[c].y, o.y));
   }
 }
 
@@ -123,22 +179,24 @@ __device__ __forceinline__ void line_transform(const float2 (&v)[kNZ], float2 (&
 template <bool FULL>
 __global__ __launch_bounds__(kLines * kP) void psf_rows_kernel(const PsfLaunch a, int64_t f0, int nf, int64_t nrows,
                                                                float2* __restrict__ T) {
-  __shared__ float s_pl[kLines * kQ * kST];
+  __shared__ float s_pl[kLines * kPlane];
   const int tid = threadIdx.x;
-  const int line = tid / kP, j = tid - line * kP;
-  const int q = j >> 1, h = j & 1;
+  int q, h, line;
+  lane_place(tid, q, h, line);
   const int64_t row = (int64_t)blockIdx.x * kLines + line;  // (star * nf + frame - f0) * pupil_n + y
   const bool active = row < nrows;
   const int64_t sf = active ? row / a.pupil_n : 0;
   const int y = active ? (int)(row - sf * a.pupil_n) : 0;
   const int64_t star = sf / nf, fl = sf - star * nf;
-  float* pl = s_pl + line * kQ * kST;
+  float* pl = s_pl + line * kPlane;
   // field samples x = 40 n1 + q; lane h computes those with n1 = h (mod 2), then the pair swaps
   float2 v[kNZ];
   {
     const float* src = a.opd + star * a.star_stride + (f0 + fl) * a.frame_stride + (int64_t)y * a.row_pitch;
     const float by = (float)y + 0.5f - a.half_n;
     const float by2 = by * by;
+    // (-1)^(x + y) in waves: x = 40 n1 + q has the parity of q
+    const double centring = (q + y) & 1 ? 0.5 : 0.0;
     // every load is issued before any is used (at a clamped address), and the samples outside
     // the pupil, the annulus or the last block's rows are masked afterwards
     float ov[kNZ / 2];
@@ -151,20 +209,18 @@ __global__ __launch_bounds__(kLines * kP) void psf_rows_kernel(const PsfLaunch a
       const float bx = (float)x + 0.5f - a.half_n;
       const float r2 = bx * bx + by2;
       const bool lit = active & (FULL || x < a.pupil_n) & (r2 <= a.r2_outer) & (r2 >= a.r2_inner);
-      double wv = (double)ov[i] * a.inv_lambda + 0.5 * (double)(x + y);
-      wv = __builtin_amdgcn_fract(wv);  // wv - floor(wv), one instruction
+      const double wv = __builtin_amdgcn_fract(fma((double)ov[i], a.inv_lambda, centring));  // wv - floor(wv)
       // hardware sine and cosine take revolutions: exp(2 pi i wv) after the FP64 reduction
       const float fw = (float)wv;
       // a select, not a product with a 0/1 amplitude: samples outside the pupil may hold anything
       const float cw = __builtin_amdgcn_cosf(fw), sw = __builtin_amdgcn_sinf(fw);
       const float2 e = make_float2(lit ? cw : 0.0f, lit ? sw : 0.0f);
-      const float2 o = pair_swap(e);  // the partner's sample 2 i + (1 - h)
-      v[2 * i] = h ? o : e;
-      v[2 * i + 1] = h ? e : o;
+      v[2 * i] = pair_even(e);
+      v[2 * i + 1] = pair_odd(e);
     }
   }
   float2 x[kNZ];
-  line_transform(v, x, pl, q, h);
+  line_transform(v, x, pl, line_twiddles(q, h), q, h, [] {});
   if (active) {
     // column q + 40 (c + 20 h): its column block advances by 5 per c and its place in the block
     // stays q % 8, so the outputs are 40 pupil_n elements apart
@@ -181,12 +237,12 @@ template <bool FULL>
 __global__ __launch_bounds__(kLines * kP) __attribute__((amdgpu_waves_per_eu(4))) void psf_cols_kernel(const PsfLaunch a, int64_t f0, int nf,
                                                                int n_groups, const float2* __restrict__ T,
                                                                float* __restrict__ acc, float* __restrict__ strehl) {
-  __shared__ float s_pl[kLines * kQ * kST];
-  // per-line sums over the frames: lane (q, h) owns entries q + 40 (c + 20 h), c < 20 (no barrier)
-  __shared__ float s_sum[kLines][kM];
+  __shared__ float s_pl[kLines * kPlane];
+  // the block's columns of one frame, as they lie in the intermediate: [row][kLines]
+  __shared__ __align__(16) float2 s_in[kM / 2 * kLines];
   const int tid = threadIdx.x;
-  const int line = tid / kP, j = tid - line * kP;
-  const int q = j >> 1, h = j & 1;
+  int q, h, line;
+  lane_place(tid, q, h, line);
   const int b = blockIdx.x;
   const int m = (b >> 3) & 7;
   const int g = (b >> 6) * 8 + (b & 7);
@@ -195,46 +251,77 @@ __global__ __launch_bounds__(kLines * kP) __attribute__((amdgpu_waves_per_eu(4))
   const int star = g / kGroups;
   const int u0 = (g - star * kGroups) * kGroupCols + m * kLines;  // first column of the block
   const int u = u0 + line;
-  float* pl = s_pl + line * kQ * kST;
-  float* sum = s_sum[line];
+  float* pl = s_pl + line * kPlane;
+  // Reads a frame's columns (contiguous, 16 bytes a lane) straight into LDS.  A lane's place there is
+  // its number, so it picks what to read: 16-byte unit P holds columns 2 ((P >> 3) & 1) .. + 1 of row
+  // 8 (P >> 4) + (P & 7), and the 8 rows that a wavefront reads together below lie in 8 different bank quads.
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rows = FULL ? kM / 2 : a.pupil_n;
+  const int row0 = (tid >> 4) * 8 + (tid & 7);  // row of the lane's first unit; the next ones are kFetchRows on
+  constexpr int kFetchRows = kLines * kP / 2;
+  const uint32_t lane_off = (uint32_t)(row0 * kLines + 2 * ((tid >> 3) & 1)) * sizeof(float2);
+  auto fetch = [&](int fl) {
+    using GlobalC = __attribute__((address_space(1))) const char;
+    const GlobalC* src = (const GlobalC*)(T + t_index((int64_t)star * nf + fl, a.pupil_n, 0, u0));
 #pragma unroll
-  for (int c = 0; c < kNZ; ++c) sum[q + kQ * (c + kNZ * h)] = 0.0f;
+    for (int i = 0; i < kFetch; ++i) {
+      constexpr int kBytes = 16 * kLines * kP;  // per step of the block
+      if (FULL || i * kFetchRows + row0 < rows)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + i * kBytes + lane_off),
+                                         (__attribute__((address_space(3))) void*)((char*)s_in + i * kBytes + wave * 1024),
+                                         16, 0, 0);
+    }
+  };
+  // row 40 n1 + q of the lane's column: q = 8 (q >> 3) + (q & 7)
+  const float2* in = s_in + (q >> 3) * 32 + (line >> 1) * 16 + (q & 7) * 2 + (line & 1);
+  const LineTwiddles tw = line_twiddles(q, h);
+  float sum[kNZ];  // of output q + 40 (c + 20 h)
+#pragma unroll
+  for (int c = 0; c < kNZ; ++c) sum[c] = 0.0f;
+  fetch(0);
   for (int fl = 0; fl < nf; ++fl) {
-    const int64_t sf = (int64_t)star * nf + fl;
-    // rows 40 n1 + q of column u, 40 x 8 elements apart; with FULL every row is inside the pupil
-    const float2* src = T + t_index(sf, a.pupil_n, q, u);
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wavefront's part of the columns is in LDS
+    __syncthreads();
+    // rows 40 n1 + q of column u; with FULL every row is inside the pupil
     float2 v[kNZ];
 #pragma unroll
     for (int n1 = 0; n1 < kNZ; ++n1)
-      v[n1] = FULL || kQ * n1 + q < a.pupil_n ? src[n1 * kQ * kCB] : make_float2(0.0f, 0.0f);
+      v[n1] = FULL || kQ * n1 + q < rows ? in[kQ * n1 * kLines] : make_float2(0.0f, 0.0f);
     float2 x[kNZ];
-    line_transform(v, x, pl, q, h);
+    line_transform(v, x, pl, tw, q, h, [&] {
+      if (fl + 1 < nf) fetch(fl + 1);
+    });
 #pragma unroll
-    for (int c = 0; c < kNZ; ++c) {
-      const float p = (x[c].x * x[c].x + x[c].y * x[c].y) * a.inv_norm;
-      sum[q + kQ * (c + kNZ * h)] += p;
-      // on-axis sample: v = u = M/2, i.e. k1 = 0, k2 = 20 (c = 0, h = 1) of column M/2
-      if (strehl && u == kM / 2 && q == 0 && h == 1 && c == 0) strehl[(int64_t)star * a.n_frames + f0 + fl] = p;
-    }
+    for (int c = 0; c < kNZ; ++c) sum[c] = fmaf(x[c].y, x[c].y, fmaf(x[c].x, x[c].x, sum[c]));
+    // on-axis sample: v = u = M/2, i.e. k1 = 0, k2 = 20 (c = 0, h = 1) of column M/2
+    if (strehl && u == kM / 2 && q == 0 && h == 1)
+      strehl[(int64_t)star * a.n_frames + f0 + fl] = (x[0].x * x[0].x + x[0].y * x[0].y) * a.inv_norm;
   }
-  __syncthreads();  // every line's sums are in LDS
+  // the sums of the four lines side by side in LDS (the last transform has read the plane)
+  float* s_sum = s_pl;
+#pragma unroll
+  for (int c = 0; c < kNZ; ++c) s_sum[line * kSumStride + q + kQ * c + kHalf * h] = sum[c];
+  __syncthreads();
   // accumulator rows v, columns u0 .. u0 + 3: one 16-byte read-modify-write per row when the
   // accumulator allows it (u0 is a multiple of 4), else four 4-byte ones
   float* ac = acc + star * a.acc_stride + u0;
   if ((reinterpret_cast<uintptr_t>(ac) & 15) == 0) {
     for (int vv = tid; vv < kM; vv += kLines * kP) {
       float4* pa = reinterpret_cast<float4*>(ac + (int64_t)vv * kM);
+      const int at = vv < kM / 2 ? vv : vv + (kHalf - kM / 2);
       float4 o = *pa;
-      o.x += s_sum[0][vv];
-      o.y += s_sum[1][vv];
-      o.z += s_sum[2][vv];
-      o.w += s_sum[3][vv];
+      o.x = fmaf(s_sum[at], a.inv_norm, o.x);
+      o.y = fmaf(s_sum[kSumStride + at], a.inv_norm, o.y);
+      o.z = fmaf(s_sum[2 * kSumStride + at], a.inv_norm, o.z);
+      o.w = fmaf(s_sum[3 * kSumStride + at], a.inv_norm, o.w);
       *pa = o;
     }
   } else {
     for (int e = tid; e < kM * kLines; e += kLines * kP) {
       const int vv = e >> 2, l = e & 3;
-      ac[(int64_t)vv * kM + l] += s_sum[l][vv];
+      const int at = vv < kM / 2 ? vv : vv + (kHalf - kM / 2);
+      float* pa = ac + (int64_t)vv * kM + l;
+      *pa = fmaf(s_sum[l * kSumStride + at], a.inv_norm, *pa);
     }
   }
 }

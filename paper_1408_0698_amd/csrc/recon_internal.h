@@ -6,11 +6,10 @@
 
 namespace shw {
 
-constexpr int kReconRows = 64;     // control-matrix rows per block (16 per wave)
 constexpr int kReconCols = 4096;   // slope columns per block (staged in LDS)
 
 // Number of column chunks of a product with n_slopes columns.
-inline int recon_chunks(int64_t n_slopes) { return (int)((n_slopes + kReconCols - 1) / kReconCols); }
+__host__ __device__ inline int recon_chunks(int64_t n_slopes) { return (int)((n_slopes + kReconCols - 1) / kReconCols); }
 
 // partial[chunk][m] = sum over the chunk's columns s of cm[m * ld + s] * slopes[s].
 hipError_t launch_recon_partial(const float* cm, int64_t ld, int32_t n_modes, int32_t n_slopes, const float* slopes,

@@ -1211,7 +1211,7 @@ __device__ __forceinline__ float2 rotate(float2 x, int j) {
 // Bound by HBM for many frames: 4096 frames of 80 sub-apertures (107 MB) without images take 26.7 us,
 // 4.0 TB/s; the two-dimensional transform on 16 lanes per sub-aperture, every phase formed twice and
 // the centroid added by one lane, took 84 us.  FP32 sums throughout would take 24.6 us (error against
-// 64 bits 1.0e-7 instead of 6.4e-8), FP64 products 30.4 us (6.3e-8).
+// 64 bits 1.0e-7 instead of 5.5e-8), FP64 products 30.4 us.
 constexpr int kNgsWaves = 4;
 template <int DN, bool IMG>
 __global__ __launch_bounds__(64 * kNgsWaves) void wfs_ngs8_kernel(const WfsLaunch a) {
@@ -1265,11 +1265,11 @@ __global__ __launch_bounds__(64 * kNgsWaves) void wfs_ngs8_kernel(const WfsLaunc
   const double s0 = sum8((double)tot), sx = sum8(mx), sy = sum8(my);
   if (active && y < 2) {
     const bool empty = !(s0 > 0.0);
-    // the quotient by the hardware reciprocal, corrected by its remainder: rounded almost correctly
-    const float num = (float)(y == 0 ? sx : sy), den = (float)s0;
-    const float r = __builtin_amdgcn_rcpf(den);
-    const float v0 = num * r;
-    const float v = empty ? 0.0f : fmaf(fmaf(-den, v0, num), r, v0);
+    // the quotient by the hardware reciprocal, corrected by its FP64 remainder: one rounding to FP32
+    const double num = y == 0 ? sx : sy;
+    const float r = __builtin_amdgcn_rcpf((float)s0);
+    const double v0 = (double)((float)num * r);
+    const float v = empty ? 0.0f : (float)fma(fma(-s0, v0, num), (double)r, v0);
     ref.slopes_fw[y * a.n_valid + ref.i] = v;
     if (y == 0 && a.flags && !a.list) a.flags[item] = empty ? 1 : 0;
   }
@@ -1277,15 +1277,19 @@ __global__ __launch_bounds__(64 * kNgsWaves) void wfs_ngs8_kernel(const WfsLaunc
     const float scale = (a.ph_scale > 0.0f ? a.ph_scale : 1.0f) / (float)(N * N);
     float det[DN / 8][DN];  // this lane's detector columns
 #pragma unroll
-    for (int q = 0; q < DN / 8; ++q)
-#pragma unroll
-      for (int p = 0; p < DN; ++p) det[q][p] = 0.0f;
-#pragma unroll
     for (int k2 = 0; k2 < 2; ++k2) {
-      // row transform, columns u = 2 k1 + k2: 8-point transforms of e(x) exp(2 pi i ((N-1)/2 - k2) x / N)
+      // row transform, columns u = 2 k1 + k2: 8-point transforms of e(x) exp(2 pi i ((N-1)/2 - k2) x / N).  That
+      // factor and the columns' half-sample shift go into the phase, which is formed anew: as rotations of every
+      // term they cost two roundings (image error against 64 bits 1.8e-7 instead of 1.2e-7)
       float2 z[NPX];
 #pragma unroll
-      for (int x = 0; x < NPX; ++x) z[x] = rotate<2 * N>(e[x], (N - 1 - 2 * k2) * x);
+      for (int x = 0; x < NPX; ++x) {
+        const double shift = (double)((N - 1 - 2 * k2) * x + (N - 1) * y) / (2 * N);
+        const float fw =
+            (float)__builtin_amdgcn_fract(fma((double)(x < 4 ? q0[x & 3] : q1[x & 3]), a.inv_lambda, shift));
+        const float amp = e[x].x == 0.0f && e[x].y == 0.0f ? 0.0f : 1.0f;
+        z[x] = make_float2(amp * __builtin_amdgcn_cosf(fw), amp * __builtin_amdgcn_sinf(fw));
+      }
       RegFFT<NPX, -1>::run(z);
       __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
       __builtin_amdgcn_wave_barrier();  // the tile's previous contents have been read
@@ -1296,17 +1300,24 @@ __global__ __launch_bounds__(64 * kNgsWaves) void wfs_ngs8_kernel(const WfsLaunc
       float2 g[NPX];  // column u = 2 lane + k2
 #pragma unroll
       for (int k = 0; k < NPX; ++k) g[k] = tile[k * RS + y];
+      float pair[NPX];  // of 8-pixel detectors: the two rows of each pixel
 #pragma unroll
       for (int v2 = 0; v2 < 2; ++v2) {
 #pragma unroll
-        for (int k = 0; k < NPX; ++k) z[k] = rotate<2 * N>(g[k], (N - 1 - 2 * v2) * k);
+        for (int k = 0; k < NPX; ++k) z[k] = rotate<N>(g[k], -v2 * k);
         RegFFT<NPX, -1>::run(z);
 #pragma unroll
         for (int k = 0; k < NPX; ++k) {  // row v = 2 k + v2
-          float& d = DN == N ? det[k2 % (DN / 8)][(2 * k + v2) % DN] : det[0][k % DN];
-          d = fmaf(z[k].x, z[k].x, d);
-          d = fmaf(z[k].y, z[k].y, d);
+          const float d = fmaf(z[k].y, z[k].y, z[k].x * z[k].x);
+          if (DN == N)
+            det[k2 % (DN / 8)][(2 * k + v2) % DN] = d;
+          else
+            pair[k] = v2 ? pair[k] + d : d;
         }
+      }
+      if (DN != N) {
+#pragma unroll
+        for (int k = 0; k < NPX; ++k) det[0][k] = k2 ? det[0][k] + pair[k] : pair[k];
       }
     }
     if (active && ref.images_it) {

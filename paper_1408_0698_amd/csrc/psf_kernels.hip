@@ -26,18 +26,19 @@
 // at ((f * M/4 + u/4) * pupil_n + y) * 4 + u % 4, and a wavefront holds 8 consecutive outputs of all four rows,
 // so that every store writes whole 128-byte lines (runs of 64 bytes, one row at a time, are written
 // at 3.4 TB/s on this card, whole lines at 5.8; the stores alone took 650 us of 9 x 20 star-frames).
-// Column pass: 4 columns per block, which are one contiguous region of T.  It is read straight into LDS, 16
-// bytes a lane, the next frame's while this one is transformed; the frames' sums stay in registers
+// Column pass: 4 columns per block, which are one contiguous region of T.  Each wavefront reads the rows it
+// transforms straight into LDS, 16 bytes a lane, before it needs them; the frames' sums stay in LDS
 // (each lane owns its 20 outputs), then one read-modify-write of the accumulator per call, 16 bytes
 // (the block's 4 columns) per row, the 8 blocks of a 32-column group (one 128-byte line of every
 // accumulator row) launched 8 apart, so that the dispatcher places them on one XCD and its L2 merges
-// their writes; the on-axis sample of each frame is the Strehl ratio.  A 4-waves-per-
-// SIMD register target (128 VGPRs) lets 3 blocks share a CU; at 2 blocks (3 waves per SIMD, no spills) the pass
-// takes 1.17 instead of 0.88 ms.
-// 9 stars x 20 frames: 1.24 ms for both passes (traced: rows 0.56 ms, at 4.1 TB/s; columns 0.88 ms).  The rows are
-// bound by HBM; the columns by issue and the five barriers of a frame (with the reads taken out they took
-// 0.67 ms).  1.51 ms with T in column blocks of 8, one row or column per 80 consecutive lanes and each
-// lane reading its column with 64-byte strides.
+// their writes; the on-axis sample of each frame is the Strehl ratio.  At 75 registers 3 blocks share a CU.
+// With the sums in registers (124) only 2 do, because a CU takes 5-wavefront blocks only while every SIMD
+// has room for 2 more of their wavefronts: 0.81 instead of 0.72 ms, and as much with 3 barriers a frame
+// (transposes of complex values) as with 4.
+// 9 stars x 20 frames: 1.20 ms for both passes (traced: rows 0.58 ms, at 4.0 TB/s; columns 0.72 ms).  The rows are
+// bound by HBM; the columns by issue (with the reads taken out they took 0.70 ms, the reads alone 0.44).
+// 1.51 ms with T in column blocks of 8, one row or column per 80 consecutive lanes and each lane reading its
+// column with 64-byte strides.
 // Both passes have a form for pupil_n = M/2 (the Nyquist-sampled PSF), where
 // every sample of the pruned transforms lies in the pupil grid, so its loads
 // need no bounds masks.
@@ -66,7 +67,7 @@ constexpr int kSumStride = kM + 16;
 constexpr int kCB = kLines;       // columns per block of the intermediate
 constexpr int kFetch = kM / 2 * kLines * (int)sizeof(float2) / (16 * kLines * kP);  // 16-byte reads per lane and frame
 static_assert(kFetch * 16 * kLines * kP == kM / 2 * kLines * (int)sizeof(float2), "a frame's columns in whole reads");
-static_assert(kLines * kSumStride <= kLines * kPlane, "the sums fit the transposes' planes");
+static_assert(kLines * kP / 64 * kFetch * 16 * 64 <= kLines * kPlane * (int)sizeof(float), "the columns fit the transposes' planes");
 constexpr int kGroupCols = 32;    // columns per 128-byte accumulator line (8 column-pass blocks)
 
 // Offset of element (star-frame sf, row y, column u) of the intermediate.
@@ -115,10 +116,10 @@ __device__ __forceinline__ LineTwiddles line_twiddles(int q, int h) {
 // One M-point transform of a line with at most M/2 non-zero inputs v[n1] (sample 40 n1 + q),
 // on lane pair (q, h) of the line; pl is the line's LDS plane.  On return lane (q, h) holds
 // X[q + 40 (c + 20 h)] in x[c], c < 20.  Every lane of the block must call it.
-// `staged` runs once every lane of the block has the values it needed for v.
+// `moved` runs once every lane of the block has read the plane.
 template <class F>
 __device__ __forceinline__ void line_transform(const float2 (&v)[kNZ], float2 (&x)[kNZ], float* pl,
-                                               const LineTwiddles& tw, int q, int h, F staged) {
+                                               const LineTwiddles& tw, int q, int h, F moved) {
   float2 z[kNZ];
 #pragma unroll
   for (int n1 = 0; n1 < kNZ; ++n1) z[n1] = v[n1];
@@ -143,12 +144,11 @@ __device__ __forceinline__ void line_transform(const float2 (&v)[kNZ], float2 (&
     }
   }
   // transpose: lane (n2, h) holds Y[2k + h]; lane (k1, h) takes samples n2 = 2t + h
-  float* wr = pl + plane_at(h, q);   // row 2k + h is 84 k further on
+  float* wr = pl + plane_at(h, q);        // row 2k + h is 84 k further on
   const float* rd = pl + plane_at(q, h);  // column 2t + h is 4 t further on
 #pragma unroll
   for (int k = 0; k < kNZ; ++k) wr[84 * k] = z[k].x;
   __syncthreads();
-  staged();
 #pragma unroll
   for (int t = 0; t < kNZ; ++t) x[t].x = rd[4 * t];
   __syncthreads();
@@ -158,6 +158,7 @@ __device__ __forceinline__ void line_transform(const float2 (&v)[kNZ], float2 (&
 #pragma unroll
   for (int t = 0; t < kNZ; ++t) x[t].y = rd[4 * t];
   __syncthreads();
+  moved();
   RegFFT<kNZ, -1>::run(x);
   if (h) {
 #pragma unroll
@@ -237,9 +238,10 @@ template <bool FULL>
 __global__ __launch_bounds__(kLines * kP) __attribute__((amdgpu_waves_per_eu(4))) void psf_cols_kernel(const PsfLaunch a, int64_t f0, int nf,
                                                                int n_groups, const float2* __restrict__ T,
                                                                float* __restrict__ acc, float* __restrict__ strehl) {
-  __shared__ float s_pl[kLines * kPlane];
-  // the block's columns of one frame, as they lie in the intermediate: [row][kLines]
-  __shared__ __align__(16) float2 s_in[kM / 2 * kLines];
+  // the transposes' planes; before them each wavefront's part of the columns of a frame
+  __shared__ __align__(16) float s_pl[kLines * kPlane];
+  // per-line sums over the frames; each lane owns its outputs' (in registers they would cost a third block per CU)
+  __shared__ float s_sum[kLines * kSumStride];
   const int tid = threadIdx.x;
   int q, h, line;
   lane_place(tid, q, h, line);
@@ -252,55 +254,56 @@ __global__ __launch_bounds__(kLines * kP) __attribute__((amdgpu_waves_per_eu(4))
   const int u0 = (g - star * kGroups) * kGroupCols + m * kLines;  // first column of the block
   const int u = u0 + line;
   float* pl = s_pl + line * kPlane;
-  // Reads a frame's columns (contiguous, 16 bytes a lane) straight into LDS.  A lane's place there is
+  // Reads the rows 40 n1 + q of a frame's columns that this wavefront transforms straight into LDS, 16
+  // bytes a lane (8 rows of the block's columns, 256 bytes, lie together).  A lane's place there is
   // its number, so it picks what to read: 16-byte unit P holds columns 2 ((P >> 3) & 1) .. + 1 of row
-  // 8 (P >> 4) + (P & 7), and the 8 rows that a wavefront reads together below lie in 8 different bank quads.
+  // 40 (P >> 4) + 8 wave + (P & 7), and the 8 rows that a wavefront reads together below lie in 8 different
+  // bank quads.
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int rows = FULL ? kM / 2 : a.pupil_n;
-  const int row0 = (tid >> 4) * 8 + (tid & 7);  // row of the lane's first unit; the next ones are kFetchRows on
-  constexpr int kFetchRows = kLines * kP / 2;
+  const int row0 = kQ * ((tid & 63) >> 4) + (wave * 8) + (tid & 7);  // row of the lane's first unit; the next ones are kFetchRows on
+  constexpr int kFetchRows = 4 * kQ;
+  constexpr int kFetchBytes = 16 * 64;  // of LDS per step of the wavefront
+  float2* part = reinterpret_cast<float2*>(s_pl) + wave * (kFetch * kFetchBytes / (int)sizeof(float2));
   const uint32_t lane_off = (uint32_t)(row0 * kLines + 2 * ((tid >> 3) & 1)) * sizeof(float2);
   auto fetch = [&](int fl) {
     using GlobalC = __attribute__((address_space(1))) const char;
     const GlobalC* src = (const GlobalC*)(T + t_index((int64_t)star * nf + fl, a.pupil_n, 0, u0));
 #pragma unroll
     for (int i = 0; i < kFetch; ++i) {
-      constexpr int kBytes = 16 * kLines * kP;  // per step of the block
+      constexpr int kBytes = kFetchRows * kLines * (int)sizeof(float2);
       if (FULL || i * kFetchRows + row0 < rows)
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + i * kBytes + lane_off),
-                                         (__attribute__((address_space(3))) void*)((char*)s_in + i * kBytes + wave * 1024),
+                                         (__attribute__((address_space(3))) void*)((char*)part + i * kFetchBytes),
                                          16, 0, 0);
     }
   };
-  // row 40 n1 + q of the lane's column: q = 8 (q >> 3) + (q & 7)
-  const float2* in = s_in + (q >> 3) * 32 + (line >> 1) * 16 + (q & 7) * 2 + (line & 1);
+  // row 40 n1 + q of the lane's column, 32 n1 further on
+  const float2* in = part + (line >> 1) * 16 + (q & 7) * 2 + (line & 1);
   const LineTwiddles tw = line_twiddles(q, h);
-  float sum[kNZ];  // of output q + 40 (c + 20 h)
+  float* sum = s_sum + line * kSumStride + q + kHalf * h;  // output q + 40 (c + 20 h) is 40 c further on
 #pragma unroll
-  for (int c = 0; c < kNZ; ++c) sum[c] = 0.0f;
+  for (int c = 0; c < kNZ; ++c) sum[kQ * c] = 0.0f;
   fetch(0);
   for (int fl = 0; fl < nf; ++fl) {
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wavefront's part of the columns is in LDS
-    __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     // rows 40 n1 + q of column u; with FULL every row is inside the pupil
     float2 v[kNZ];
 #pragma unroll
     for (int n1 = 0; n1 < kNZ; ++n1)
-      v[n1] = FULL || kQ * n1 + q < rows ? in[kQ * n1 * kLines] : make_float2(0.0f, 0.0f);
+      v[n1] = FULL || kQ * n1 + q < rows ? in[32 * n1] : make_float2(0.0f, 0.0f);
+    __syncthreads();  // every wavefront has read its part
     float2 x[kNZ];
     line_transform(v, x, pl, tw, q, h, [&] {
       if (fl + 1 < nf) fetch(fl + 1);
     });
 #pragma unroll
-    for (int c = 0; c < kNZ; ++c) sum[c] = fmaf(x[c].y, x[c].y, fmaf(x[c].x, x[c].x, sum[c]));
+    for (int c = 0; c < kNZ; ++c) sum[kQ * c] = fmaf(fmaf(x[c].x, x[c].x, x[c].y * x[c].y), a.inv_norm, sum[kQ * c]);
     // on-axis sample: v = u = M/2, i.e. k1 = 0, k2 = 20 (c = 0, h = 1) of column M/2
     if (strehl && u == kM / 2 && q == 0 && h == 1)
-      strehl[(int64_t)star * a.n_frames + f0 + fl] = (x[0].x * x[0].x + x[0].y * x[0].y) * a.inv_norm;
+      strehl[(int64_t)star * a.n_frames + f0 + fl] = fmaf(x[0].x, x[0].x, x[0].y * x[0].y) * a.inv_norm;
   }
-  // the sums of the four lines side by side in LDS (the last transform has read the plane)
-  float* s_sum = s_pl;
-#pragma unroll
-  for (int c = 0; c < kNZ; ++c) s_sum[line * kSumStride + q + kQ * c + kHalf * h] = sum[c];
   __syncthreads();
   // accumulator rows v, columns u0 .. u0 + 3: one 16-byte read-modify-write per row when the
   // accumulator allows it (u0 is a multiple of 4), else four 4-byte ones
@@ -310,10 +313,10 @@ __global__ __launch_bounds__(kLines * kP) __attribute__((amdgpu_waves_per_eu(4))
       float4* pa = reinterpret_cast<float4*>(ac + (int64_t)vv * kM);
       const int at = vv < kM / 2 ? vv : vv + (kHalf - kM / 2);
       float4 o = *pa;
-      o.x = fmaf(s_sum[at], a.inv_norm, o.x);
-      o.y = fmaf(s_sum[kSumStride + at], a.inv_norm, o.y);
-      o.z = fmaf(s_sum[2 * kSumStride + at], a.inv_norm, o.z);
-      o.w = fmaf(s_sum[3 * kSumStride + at], a.inv_norm, o.w);
+      o.x += s_sum[at];
+      o.y += s_sum[kSumStride + at];
+      o.z += s_sum[2 * kSumStride + at];
+      o.w += s_sum[3 * kSumStride + at];
       *pa = o;
     }
   } else {
@@ -321,7 +324,7 @@ __global__ __launch_bounds__(kLines * kP) __attribute__((amdgpu_waves_per_eu(4))
       const int vv = e >> 2, l = e & 3;
       const int at = vv < kM / 2 ? vv : vv + (kHalf - kM / 2);
       float* pa = ac + (int64_t)vv * kM + l;
-      *pa = fmaf(s_sum[l * kSumStride + at], a.inv_norm, *pa);
+      *pa += s_sum[l * kSumStride + at];
     }
   }
 }

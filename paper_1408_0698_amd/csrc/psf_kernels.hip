@@ -31,12 +31,12 @@
 // (each lane owns its 20 outputs), then one read-modify-write of the accumulator per call, 16 bytes
 // (the block's 4 columns) per row, the 8 blocks of a 32-column group (one 128-byte line of every
 // accumulator row) launched 8 apart, so that the dispatcher places them on one XCD and its L2 merges
-// their writes; the on-axis sample of each frame is the Strehl ratio.  At 75 registers 3 blocks share a CU.
-// With the sums in registers (124) only 2 do, because a CU takes 5-wavefront blocks only while every SIMD
-// has room for 2 more of their wavefronts: 0.81 instead of 0.72 ms, and as much with 3 barriers a frame
-// (transposes of complex values) as with 4.
-// 9 stars x 20 frames: 1.20 ms for both passes (traced: rows 0.58 ms, at 4.0 TB/s; columns 0.72 ms).  The rows are
-// bound by HBM; the columns by issue (with the reads taken out they took 0.70 ms, the reads alone 0.44).
+// their writes; the on-axis sample of each frame is the Strehl ratio.  With at most 96 registers 3 blocks
+// share a CU.  With more (the sums in registers: 124) only 2 do, because a CU takes 5-wavefront blocks only
+// while every SIMD has room for 2 more of their wavefronts: 0.81 to 0.85 instead of 0.71 ms, and as much with 3
+// barriers a frame (transposes of complex values) as with 4.
+// 9 stars x 20 frames: 1.08 ms for both passes (traced: rows 0.57 ms, at 4.1 TB/s; columns 0.71 ms).  The rows are
+// bound by HBM; the columns by issue (with the reads taken out they took 0.66 ms, the reads alone 0.44).
 // 1.51 ms with T in column blocks of 8, one row or column per 80 consecutive lanes and each lane reading its
 // column with 64-byte strides.
 // Both passes have a form for pupil_n = M/2 (the Nyquist-sampled PSF), where
@@ -69,6 +69,8 @@ constexpr int kFetch = kM / 2 * kLines * (int)sizeof(float2) / (16 * kLines * kP
 static_assert(kFetch * 16 * kLines * kP == kM / 2 * kLines * (int)sizeof(float2), "a frame's columns in whole reads");
 static_assert(kLines * kP / 64 * kFetch * 16 * 64 <= kLines * kPlane * (int)sizeof(float), "the columns fit the transposes' planes");
 constexpr int kGroupCols = 32;    // columns per 128-byte accumulator line (8 column-pass blocks)
+
+typedef float float2v __attribute__((ext_vector_type(2)));
 
 // Offset of element (star-frame sf, row y, column u) of the intermediate.
 __device__ __forceinline__ int64_t t_index(int64_t sf, int pupil_n, int y, int u) {
@@ -235,13 +237,13 @@ __global__ __launch_bounds__(kLines * kP) void psf_rows_kernel(const PsfLaunch a
 // Column pass.  Block b = 64 j + 8 m + x takes columns 4 m .. 4 m + 3 of the 32-column group
 // g = 8 j + x (groups past the last one leave at once).
 template <bool FULL>
-__global__ __launch_bounds__(kLines * kP) __attribute__((amdgpu_waves_per_eu(4))) void psf_cols_kernel(const PsfLaunch a, int64_t f0, int nf,
+__global__ __launch_bounds__(kLines * kP) __attribute__((amdgpu_waves_per_eu(5))) void psf_cols_kernel(const PsfLaunch a, int64_t f0, int nf,
                                                                int n_groups, const float2* __restrict__ T,
                                                                float* __restrict__ acc, float* __restrict__ strehl) {
   // the transposes' planes; before them each wavefront's part of the columns of a frame
-  __shared__ __align__(16) float s_pl[kLines * kPlane];
-  // per-line sums over the frames; each lane owns its outputs' (in registers they would cost a third block per CU)
-  __shared__ float s_sum[kLines * kSumStride];
+  extern __shared__ __align__(16) float s_pl[];
+  // per-line sums over the frames; each lane owns its outputs'
+  float* const s_sum = s_pl + kLines * kPlane;
   const int tid = threadIdx.x;
   int q, h, line;
   lane_place(tid, q, h, line);
@@ -346,10 +348,13 @@ hipError_t launch_psf_cols(const PsfLaunch& a, int n_stars, int64_t f0, int nf, 
   static_assert(kGroupCols == 8 * kLines && kM % kGroupCols == 0, "8 blocks per 32-column group");
   const int n_groups = n_stars * (kM / kGroupCols);
   const dim3 cg((unsigned)(((n_groups + 7) / 8) * 64));
+  // the size is given here and not by static arrays: knowing it, the compiler counts 3 blocks as 4 wavefronts a
+  // SIMD and claims the registers that 4 may have, with which only 2 blocks fit (0.85 instead of 0.71 ms)
+  constexpr unsigned kLds = kLines * (kPlane + kSumStride) * sizeof(float);
   if (a.pupil_n == kM / 2)
-    hipLaunchKernelGGL(psf_cols_kernel<true>, cg, dim3(kLines * kP), 0, st, a, f0, nf, n_groups, T, acc, strehl);
+    hipLaunchKernelGGL(psf_cols_kernel<true>, cg, dim3(kLines * kP), kLds, st, a, f0, nf, n_groups, T, acc, strehl);
   else
-    hipLaunchKernelGGL(psf_cols_kernel<false>, cg, dim3(kLines * kP), 0, st, a, f0, nf, n_groups, T, acc, strehl);
+    hipLaunchKernelGGL(psf_cols_kernel<false>, cg, dim3(kLines * kP), kLds, st, a, f0, nf, n_groups, T, acc, strehl);
   return hipGetLastError();
 }
 

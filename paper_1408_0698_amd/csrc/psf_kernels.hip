@@ -35,7 +35,7 @@
 // share a CU.  With more (the sums in registers: 124) only 2 do, because a CU takes 5-wavefront blocks only
 // while every SIMD has room for 2 more of their wavefronts: 0.81 to 0.85 instead of 0.71 ms, and as much with 3
 // barriers a frame (transposes of complex values) as with 4.
-// 9 stars x 20 frames: 1.08 ms for both passes (traced: rows 0.57 ms, at 4.1 TB/s; columns 0.71 ms).  The rows are
+// 9 stars x 20 frames: 1.07 ms for both passes (traced: rows 0.56 ms, at 4.1 TB/s; columns 0.71 ms).  The rows are
 // bound by HBM; the columns by issue (with the reads taken out they took 0.66 ms, the reads alone 0.44).
 // 1.51 ms with T in column blocks of 8, one row or column per 80 consecutive lanes and each lane reading its
 // column with 64-byte strides.
@@ -180,22 +180,23 @@ __device__ __forceinline__ void line_transform(const float2 (&v)[kNZ], float2 (&
 
 // FULL: pupil_n = M / 2, so every sample 40 n1 + q (n1 < 20) lies inside the grid.
 template <bool FULL>
-__global__ __launch_bounds__(kLines * kP) void psf_rows_kernel(const PsfLaunch a, int64_t f0, int nf, int64_t nrows,
+__global__ __launch_bounds__(kLines * kP) void psf_rows_kernel(const PsfLaunch a, int64_t f0, int nf,
                                                                float2* __restrict__ T) {
   __shared__ float s_pl[kLines * kPlane];
   const int tid = threadIdx.x;
   int q, h, line;
   lane_place(tid, q, h, line);
-  const int64_t row = (int64_t)blockIdx.x * kLines + line;  // (star * nf + frame - f0) * pupil_n + y
-  const bool active = row < nrows;
-  const int64_t sf = active ? row / a.pupil_n : 0;
-  const int y = active ? (int)(row - sf * a.pupil_n) : 0;
-  const int64_t star = sf / nf, fl = sf - star * nf;
+  // a block's rows belong to one star-frame, so its place is worked out on the scalar unit
+  const uint32_t row_blocks = (uint32_t)(a.pupil_n + kLines - 1) / kLines;
+  const uint32_t sf = blockIdx.x / row_blocks;  // star * nf + frame - f0
+  const int y = (int)(blockIdx.x - sf * row_blocks) * kLines + line;
+  const bool active = y < a.pupil_n;
+  const uint32_t star = sf / (uint32_t)nf, fl = sf - star * (uint32_t)nf;
   float* pl = s_pl + line * kPlane;
   // field samples x = 40 n1 + q; lane h computes those with n1 = h (mod 2), then the pair swaps
   float2 v[kNZ];
   {
-    const float* src = a.opd + star * a.star_stride + (f0 + fl) * a.frame_stride + (int64_t)y * a.row_pitch;
+    const float* src = a.opd + star * a.star_stride + (f0 + fl) * a.frame_stride + (int64_t)(active ? y : 0) * a.row_pitch;
     const float by = (float)y + 0.5f - a.half_n;
     const float by2 = by * by;
     // (-1)^(x + y) in waves: x = 40 n1 + q has the parity of q
@@ -225,12 +226,14 @@ __global__ __launch_bounds__(kLines * kP) void psf_rows_kernel(const PsfLaunch a
   float2 x[kNZ];
   line_transform(v, x, pl, line_twiddles(q, h), q, h, [] {});
   if (active) {
-    // column q + 40 (c + 20 h): its column block advances by 5 per c and its place in the block
-    // stays q % 8, so the outputs are 40 pupil_n elements apart
-    float2* dst = T + t_index(sf, a.pupil_n, y, q + kQ * kNZ * h);
-    const int64_t step = (int64_t)(kQ / kCB) * a.pupil_n * kCB;
+    // column q + 40 (c + 20 h): its column block advances by 10 per c and its place in the block
+    // stays q % 4, so the outputs are 40 pupil_n elements apart (a scalar step; a star-frame is 10 MB at most)
+    using GlobalF2 = __attribute__((address_space(1))) float2v;
+    __attribute__((address_space(1))) char* base = (__attribute__((address_space(1))) char*)(T + t_index(sf, a.pupil_n, 0, 0));
+    const uint32_t at = (uint32_t)t_index(0, a.pupil_n, y, q + kQ * kNZ * h) * sizeof(float2);
+    const uint32_t step = (uint32_t)(kQ / kCB) * a.pupil_n * kCB * sizeof(float2);
 #pragma unroll
-    for (int c = 0; c < kNZ; ++c) dst[c * step] = x[c];
+    for (int c = 0; c < kNZ; ++c) *(GlobalF2*)(base + c * (size_t)step + at) = float2v{x[c].x, x[c].y};
   }
 }
 
@@ -334,12 +337,11 @@ __global__ __launch_bounds__(kLines * kP) __attribute__((amdgpu_waves_per_eu(5))
 bool psf_size_supported(int fft_m, int pupil_n) { return fft_m == kM && pupil_n >= 1 && pupil_n <= kM / 2; }
 
 hipError_t launch_psf_rows(const PsfLaunch& a, int n_stars, int64_t f0, int nf, float2* T, hipStream_t st) {
-  const int64_t nrows = (int64_t)n_stars * nf * a.pupil_n;
-  const int64_t rb = (nrows + kLines - 1) / kLines;
+  const int64_t rb = (int64_t)n_stars * nf * ((a.pupil_n + kLines - 1) / kLines);
   if (a.pupil_n == kM / 2)
-    hipLaunchKernelGGL(psf_rows_kernel<true>, dim3((unsigned)rb), dim3(kLines * kP), 0, st, a, f0, nf, nrows, T);
+    hipLaunchKernelGGL(psf_rows_kernel<true>, dim3((unsigned)rb), dim3(kLines * kP), 0, st, a, f0, nf, T);
   else
-    hipLaunchKernelGGL(psf_rows_kernel<false>, dim3((unsigned)rb), dim3(kLines * kP), 0, st, a, f0, nf, nrows, T);
+    hipLaunchKernelGGL(psf_rows_kernel<false>, dim3((unsigned)rb), dim3(kLines * kP), 0, st, a, f0, nf, T);
   return hipGetLastError();
 }
 

@@ -21,7 +21,7 @@ struct WfsLaunch {
   int64_t row_pitch, wfs_stride, frame_stride;
   const int32_t* valid_idx;  // [n_valid] row-major sub-aperture index
   const float* khat;         // [n_wfs * n_valid][conv_n/2 + 1][conv_n] (LGS) or null
-  // band-limited shapes (conv_n = fft_n = 4 npx): the in-band part of K^ that those variants read,
+  // band-limited shapes (conv_n = fft_n = 4 npx): the in-band part of K^ that those variants and the MFMA form read,
   // [n_wfs * n_valid][npx][2 npx - 1], row k < npx holding columns 0 .. npx-1 then
   // conv_n - npx + 1 .. conv_n - 1 (the frequencies 0 .. npx-1 and -(npx-1) .. -1); else null
   const float* khat_band;

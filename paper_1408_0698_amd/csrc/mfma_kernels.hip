@@ -31,6 +31,12 @@
 // as 16x16x32 steps, two 16x16x16 products side by side along k (the
 // full-rate form of gfx950's matrix cores), from a table of ready B operands
 // that the host builds and each block stages in LDS once.
+//
+// Bound by issue: matrix and other vector instructions of a SIMD hardly overlap (8 products and 32 FMAs a
+// wavefront take 0.89 of the sum of their times), and the BF16X3 form has 31 + 35 us of them in a frame of
+// six sensors with 4928 sub-apertures.  It takes 71 us traced; plain BF16 and FP16X3 47 and 89 us with the
+// noise stage (no noise drawn), 61 and 108 us when K^ came from its 21 x 40 form, of whose lines a quarter is
+// in the band, one masked value at a time (BF16X3: 77 and 83 us).  A persistent grid is slower (75-84 us).
 #include <hip/hip_runtime.h>
 
 #include "mfma_internal.h"
@@ -268,8 +274,8 @@ __device__ __forceinline__ void step_fence() { __builtin_amdgcn_sched_barrier(0)
 // This lane's entry of constant operand `op`.
 __device__ __forceinline__ const uint4* opnd(const uint4* t, int op, int lane) { return t + op * 64 + lane; }
 
-// Frequency of in-band column j (j < 19): 0..9, then -9..-1.
-__device__ __forceinline__ int band_k(int j) { return j <= 9 ? j : j - 19; }
+// In-band kernel spectra, row j1 and column j2 for the frequencies k(j1), k(j2).
+constexpr int kBandRows = 10, kBandCols = 19;
 
 }  // namespace
 
@@ -394,22 +400,21 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(4))
       Hi[tj] = acc_value(ai);
     }
   }
-  // ---------------------------------------------------------------- J^ = I^ . K^ (rows j1 < 10; other rows and
-  // columns j2 >= 19 meet zero rows of the map tables)
+  // ---------------------------------------------------------------- J^ = I^ . K^ (rows j1 >= 10 and
+  // columns j2 >= 19 are finite and meet zero rows of the map tables)
   if constexpr (LGS) {
-    // rows k = 0..20 of the stored half spectrum, which carries the 1/N^2 of a full inverse
-    // transform; the map tables carry their own 1/N each, so the stored value is scaled by N^2
-    const float* kh = a.khat + (int64_t)(w * a.n_valid + i) * 21 * kN;
+    // the stored band [10][19] carries the 1/N^2 of a full inverse transform; the map tables carry their own
+    // 1/N each, so the stored value is scaled by N^2.  Lanes outside the band read a value inside it
+    const float* kh = a.khat_band + (int64_t)(w * a.n_valid + i) * (kBandRows * kBandCols);
+    const float* rows01 = kh + min(lr, kBandRows - 2) * kBandCols;                  // + r, r < 2
+    const float* rows23 = kh + (lr < kBandRows - 2 ? lr : kBandRows - 4) * kBandCols;  // + r, r >= 2
     float kv[2][4];
 #pragma unroll
-    for (int tj = 0; tj < 2; ++tj)
+    for (int tj = 0; tj < 2; ++tj) {
+      const int col = tj ? min(16 + lc, kBandCols - 1) : lc;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int j1 = lr + r, j2 = 16 * tj + lc;
-        const bool in = j1 < 10 && j2 < 19;
-        const int col = (band_k(j2) + kN) % kN;
-        kv[tj][r] = in ? (float)(kN * kN) * kh[j1 * kN + col] : 0.0f;
-      }
+      for (int r = 0; r < 4; ++r) kv[tj][r] = (float)(kN * kN) * (r < 2 ? rows01 : rows23)[r * kBandCols + col];
+    }
 #pragma unroll
     for (int tj = 0; tj < 2; ++tj)
 #pragma unroll

@@ -67,7 +67,7 @@ struct shw_wfs_plan {
   int32_t* d_valid = nullptr;
   int32_t* d_inv = nullptr;      // shapes with calibration pairs: number of each valid sub-aperture, in d_valid's block
   float* d_khat = nullptr;
-  float* d_khat_band = nullptr;  // in-band K^ rows of the band-limited variants, or null
+  float* d_khat_band = nullptr;  // in-band K^ rows of the band-limited variants and the MFMA form, or null
   size_t bytes = 0;
   std::vector<int32_t> valid;
   int32_t variant = 0;
@@ -527,7 +527,7 @@ static int plan_create(const shw_wfs_config* cfg, int32_t n_wfs, const shw_lgs_g
     if (e == hipSuccess) e = hipMemcpy(d_params, params.data(), sizeof(double) * params.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMalloc(&p->d_khat, sizeof(float) * (size_t)n * H * cfg->conv_n);
     if (e == hipSuccess) e = launch_lgs_spectra(cfg->conv_n, d_params, n, p->d_khat, nullptr);
-    // the band-limited variants read only the in-band part of K^, kept as a compact copy
+    // the band-limited variants and the MFMA form read only the in-band part of K^, kept as a compact copy
     const int npx = p->npx;
     const bool band = cfg->fft_n == cfg->conv_n && cfg->conv_n == 4 * npx;
     const size_t band_floats = band ? (size_t)n * npx * (2 * npx - 1) : 0;

@@ -96,8 +96,8 @@ bool wfs_shape_supported(const WfsShape& s);
 // Number of compiled launch variants of a shape (0 if unsupported).
 int wfs_variant_count(const WfsShape& s);
 
-// Variant a new plan starts with (the autotuner may pick another).
-int wfs_default_variant(const WfsShape& s);
+// Variant a new plan starts with (the autotuner may pick another); items: work items of one frame of all sensors.
+int wfs_default_variant(const WfsShape& s, int64_t items);
 // Parameters of variant v: {convolution form (0 whole rows, 1 split rows, 2 band-limited),
 // waves-per-EU target, persistent grid, noise in det_noise_kernel, items per block, sub-layers};
 // false if v is not a variant of the shape.

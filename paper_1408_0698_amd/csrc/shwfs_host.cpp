@@ -443,7 +443,7 @@ static int plan_create(const shw_wfs_config* cfg, int32_t n_wfs, const shw_lgs_g
   }
   // the valid table, then (shapes with calibration pairs) its inverse: -1 for the other sub-apertures
   std::vector<int32_t> tab = p->valid;
-  if (wfs_shape_supported(p->shape) && wfs_modes_supported(p->shape, wfs_default_variant(p->shape))) {
+  if (wfs_shape_supported(p->shape) && wfs_modes_supported(p->shape, wfs_default_variant(p->shape, (int64_t)n_wfs * p->n_valid))) {
     tab.resize((size_t)p->n_valid + (size_t)cfg->n_subap * cfg->n_subap, -1);
     for (int32_t i = 0; i < p->n_valid; ++i) tab[(size_t)p->n_valid + p->valid[i]] = i;
   }
@@ -493,7 +493,7 @@ static int plan_create(const shw_wfs_config* cfg, int32_t n_wfs, const shw_lgs_g
     p->bytes += nb;
   }
   p->big = p->prec == SHW_PREC_FP32 && !wfs_shape_supported(p->shape);
-  if (p->prec == SHW_PREC_FP32 && !p->big) p->variant = wfs_default_variant(p->shape);
+  if (p->prec == SHW_PREC_FP32 && !p->big) p->variant = wfs_default_variant(p->shape, (int64_t)n_wfs * p->n_valid);
   if (p->big) {
     // about 128 MB of row intermediates per chunk, at least one sensor frame
     const int64_t per_item = (int64_t)p->npx * cfg->fft_n * (int64_t)sizeof(float2);
@@ -1189,7 +1189,7 @@ extern "C" int shw_wfs_plan_autotune(shw_wfs_plan* p, const float* d_opd_m, int6
   }
   float best_ms = 0.0f;
   int32_t best_v = 0;
-  const int32_t def_v = p->big ? 0 : wfs_default_variant(p->shape);
+  const int32_t def_v = p->big ? 0 : wfs_default_variant(p->shape, (int64_t)p->n_wfs * p->n_valid);
   float def_ms = -1.0f;
   int rc = SHW_OK;
   for (int v = 0; v < n && rc == SHW_OK; ++v) {

@@ -1059,12 +1059,16 @@ __global__ __launch_bounds__(SPB * CONV_N) __attribute__((amdgpu_waves_per_eu(WP
   // with noise in the band-limited kernel a wavefront leaves before the others: one group only
   static_assert(!(BL && !DSPLIT && PERSIST), "band-limited noise stage: one-shot grid");
   using LY = FusedLayout<NPX, FFT_N, CONV_N, DET_N, SPLIT, DSPLIT, BL>;
-  __shared__ __align__(16) float s_re[SPB * LY::PLANE];
-  __shared__ __align__(16) float s_im[SPB * LY::PLANE];
+  // split rows: the size of the LDS is given at launch.  Knowing that 3 blocks fill it, the compiler counts 4
+  // wavefronts a SIMD and claims the registers that 4 may have; with those a CU takes only 2 blocks (a block of 5
+  // wavefronts starts only while every SIMD has room for 2 of them)
+  extern __shared__ __align__(16) float s_dyn[];
+  __shared__ __align__(16) float s_stat[SPLIT ? 4 : 2 * SPB * LY::PLANE];
+  float* const s_re = SPLIT ? s_dyn : s_stat;
+  float* const s_im = s_re + SPB * LY::PLANE;
   // band-limited kernels: W_N^(q c) = exp(-2 pi i q c / N), q < 4, c < N/4 (first read after a
   // barrier)
-  constexpr int QTW = BL ? CONV_N : 1;
-  __shared__ float2 s_qtw[QTW];
+  float2* const s_qtw = reinterpret_cast<float2*>(s_im + SPB * LY::PLANE);
   if constexpr (BL) {
     constexpr TwiddleTable<CONV_N> tw{};
     if ((int)threadIdx.x < CONV_N) {
@@ -1360,6 +1364,9 @@ template <int NPX, int FFT_N, int CONV_N, int DET_N, bool LGS, int SPB, int WPE,
           bool SUB = false, bool DSPLIT = false, bool BL = false>
 static hipError_t launch_variant(const WfsLaunch& a0, hipStream_t st) {
   auto kern = wfs_fused_kernel<NPX, FFT_N, CONV_N, DET_N, LGS, SPB, WPE, PERSIST, SPLIT, SUB, DSPLIT, BL>;
+  using LY = FusedLayout<NPX, FFT_N, CONV_N, DET_N, SPLIT, DSPLIT, BL>;
+  static_assert(!BL || SPLIT, "the band-limited twiddles lie behind the planes");
+  constexpr unsigned kLds = SPLIT ? 2 * SPB * LY::PLANE * sizeof(float) + (BL ? CONV_N * sizeof(float2) : 0) : 0;
   int64_t resident = 0;
   if constexpr (PERSIST) {
     static int per_dev = 0;  // blocks resident on the device for this kernel (per process, device 0 shape)
@@ -1367,7 +1374,7 @@ static hipError_t launch_variant(const WfsLaunch& a0, hipStream_t st) {
       int dev = 0, cus = 0, per_cu = 0;
       hipError_t e = hipGetDevice(&dev);
       if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-      if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, SPB * CONV_N, 0);
+      if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, SPB * CONV_N, kLds);
       if (e != hipSuccess) return e;
       per_dev = (per_cu > 0 ? per_cu : 1) * cus;
     }
@@ -1382,7 +1389,7 @@ static hipError_t launch_variant(const WfsLaunch& a0, hipStream_t st) {
     a.total = a0.total - i0 < step ? a0.total : i0 + step;
     const int64_t groups = (a.total - a.item0 + SPB - 1) / SPB;
     const int64_t blocks = PERSIST && groups > resident ? resident : groups;
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(SPB * CONV_N), 0, st, a);
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(SPB * CONV_N), kLds, st, a);
     if constexpr (DSPLIT) {
       const int64_t nb = (a.total - a.item0 + 3) / 4;
       switch (a.noise_head) {
@@ -1443,7 +1450,7 @@ static hipError_t launch_one(int variant, const WfsLaunch& a, hipStream_t st) {
       case 5: return launch_variant<NPX, FFT_N, CONV_N, DET_N, LGS, SPB, 4, true, false>(a, st);
       case 6: return launch_variant<NPX, FFT_N, CONV_N, DET_N, LGS, SPB, 1, false, false, false, true>(a, st);
       case 7: return launch_variant<NPX, FFT_N, CONV_N, DET_N, LGS, SPB, 4, true, false, false, true>(a, st);
-      case 8: return launch_variant<NPX, FFT_N, CONV_N, DET_N, LGS, SPB, 1, false, true, false, true>(a, st);
+      case 8: return launch_variant<NPX, FFT_N, CONV_N, DET_N, LGS, SPB, 6, false, true, false, true>(a, st);
       case 9: return launch_variant<NPX, FFT_N, CONV_N, DET_N, LGS, SPB, 4, true, true, false, true>(a, st);
       case 10: return launch_variant<NPX, FFT_N, CONV_N, DET_N, LGS, SPB, 1, true, true, false, true>(a, st);
       case 11:
@@ -1502,7 +1509,7 @@ bool wfs_variant_params(const WfsShape& s, int v, int32_t* out) {
     int8_t form, wpe, persist, dsplit;
   };
   static constexpr Row kTuned[] = {{0, 1, 0, 0}, {0, 4, 0, 0}, {1, 1, 0, 0}, {1, 4, 0, 0}, {0, 1, 1, 0},
-                                   {0, 4, 1, 0}, {0, 1, 0, 1}, {0, 4, 1, 1}, {1, 1, 0, 1}, {1, 4, 1, 1},
+                                   {0, 4, 1, 0}, {0, 1, 0, 1}, {0, 4, 1, 1}, {1, 6, 0, 1}, {1, 4, 1, 1},
                                    {1, 1, 1, 1}, {2, 5, 1, 1}, {2, 7, 0, 1}, {2, 7, 0, 0}};
   static constexpr Row kSub[] = {{0, 1, 0, 0}, {1, 1, 0, 0}, {1, 4, 1, 1}, {2, 5, 0, 1}, {2, 6, 1, 1}};
   Row r{0, 1, 0, 0};
@@ -1517,15 +1524,18 @@ bool wfs_variant_params(const WfsShape& s, int v, int32_t* out) {
   return true;
 }
 
-int wfs_default_variant(const WfsShape& s) {
+int wfs_default_variant(const WfsShape& s, int64_t items) {
   // measured on the 6-LGS frame, with and without noise and sub-layers: the band-limited kernel
   // where the shape allows it (one-shot, noise in the same kernel: as fast as with the separate
   // noise kernel and 40 instead of 101 MB per frame; persistent with sub-layers), else split
-  // rows + detector split + persistent grid
+  // rows + detector split.  Of its two forms the one-shot grid at 80 registers runs 3 blocks per CU, the
+  // persistent one at 116 only 2, but each of its blocks is done sooner: up to 4096 items a frame (512 blocks,
+  // which run at once either way) 22.8 instead of 23.2 us (FFT 20, 2500 items), above 32.5 against 29.5 us (5600)
+  // and 114 against 93 us (29,568, no noise); FFT 40, NGS: 14.2 and 14.4 us (2336), 30.4 and 29.9 (9264)
   const bool bl = s.lgs && s.fft_n == s.conv_n && s.conv_n == 4 * s.npx;
   if (s.sub) return bl ? 4 : 2;
   if (!(s.conv_n == 40 && s.det_n == 16)) return 0;
-  return bl ? kTunedVariants + 2 : 9;
+  return bl ? kTunedVariants + 2 : (items <= 4096 ? 9 : 8);
 }
 
 bool wfs_variant_needs_det_ws(const WfsShape& s, int variant) {

@@ -201,14 +201,24 @@ __device__ __forceinline__ void detect_item(const BigLaunch& a, int64_t item0, i
     const int q = t / dn, p = t - q * dn;
     const int pix = p * dn + q;
     const float* col = jr + (int64_t)q * b * dn + p;
-    // b = 512 / det_n is a power of two: for b >= 8, eight loads in flight per step (partial sums
-    // in a fixed order), not one load per dependent addition
+    // b = 512 / det_n is a power of two: from b = 32 on 32 loads in flight per step, for 8 and 16 eight
+    // (partial sums in the same fixed order), not one load per dependent addition
     float det = 0.0f;
     if (b >= 8) {
       float ps[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-      for (int k0 = 0; k0 < b; k0 += 8) {
+      if (b >= 32) {
+        for (int k0 = 0; k0 < b; k0 += 32) {
+          float in[32];
 #pragma unroll
-        for (int r = 0; r < 8; ++r) ps[r] += col[(k0 + r) * dn];
+          for (int r = 0; r < 32; ++r) in[r] = col[(k0 + r) * dn];
+#pragma unroll
+          for (int r = 0; r < 32; ++r) ps[r & 7] += in[r];
+        }
+      } else {
+        for (int k0 = 0; k0 < b; k0 += 8) {
+#pragma unroll
+          for (int r = 0; r < 8; ++r) ps[r] += col[(k0 + r) * dn];
+        }
       }
       det = ((ps[0] + ps[1]) + (ps[2] + ps[3])) + ((ps[4] + ps[5]) + (ps[6] + ps[7]));
     } else {

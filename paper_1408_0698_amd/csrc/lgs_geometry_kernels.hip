@@ -172,12 +172,11 @@ __global__ __launch_bounds__(kUpThreads) void uplink_tilt_kernel(const UplinkLau
   const int k = blockIdx.x, tid = threadIdx.x;
   const double* g = a.lgs[k];
   if (tid < a.L.n_layers) {
-    // the beam centre at altitude h: launcher (1 - h/H) + h theta, in screen samples; the beam keeps
-    // its diameter
+    // the beam centre at altitude h: launcher (1 - h/H) + h theta; the beam keeps its diameter
     const LayerDesc& L = a.L.layer[tid];
     const double f = 1.0 - L.alt_m / g[4];
-    s_cx[tid] = L.x0 + (g[0] * f + L.alt_m * g[2]) * L.inv_pitch;
-    s_cy[tid] = L.y0 + (g[1] * f + L.alt_m * g[3]) * L.inv_pitch;
+    s_cx[tid] = g[0] * f + L.alt_m * g[2];
+    s_cy[tid] = g[1] * f + L.alt_m * g[3];
   }
   __syncthreads();
   const double step = a.d / a.n_s, r2 = 0.25 * a.d * a.d;
@@ -203,8 +202,8 @@ __global__ __launch_bounds__(kUpThreads) void uplink_tilt_kernel(const UplinkLau
       double fx[kUpGroup], fy[kUpGroup];
 #pragma unroll
       for (int q = 0; q < kUpGroup; ++q) {
-        const int ix = split_coord(fma(sx[q], L.inv_pitch, s_cx[l]), L.cols, fx[q]);
-        const int iy = split_coord(fma(sy[q], L.inv_pitch, s_cy[l]), L.rows, fy[q]);
+        const int ix = split_coord(fma(s_cx[l] + sx[q], L.inv_pitch, L.x0), L.cols, fx[q]);
+        const int iy = split_coord(fma(s_cy[l] + sy[q], L.inv_pitch, L.y0), L.rows, fy[q]);
         const float* at = L.screen + (int64_t)iy * L.pitch + ix;
         p[q] = load_pair(at, 0);
         w[q] = load_pair(at + L.pitch, 0);

@@ -17,8 +17,11 @@
 // transpose through LDS, lane (k1 = q, h) holds the samples n2 = 2t + h of
 // row k1, and the 40-point transform over n2 is split radix-2 across the
 // pair: 20-point transforms, twiddle, butterfly with the partner through
-// DPP; lane h ends with outputs k2 = c + 20 h.  A lane thus keeps 20 complex
-// values instead of 40, which keeps the kernels free of register spills.
+// DPP; lane h ends with outputs k2 = c + 20 h.  In both steps register j of an
+// odd lane stands for k or t = j + 2 mod 20: 40 = 8 x 5 without a common factor, so with that rotation
+// the odd lane's twiddles W_40^j become W_8^j, half of them trivial (80 of 950
+// instructions per column: 678 -> 638 us for 9 x 20 star-frames of 203-pixel pupils, 1098 -> 1090 of
+// 800-pixel ones on the same card).  A lane keeps 20 complex values instead of 40.
 //
 // Row pass: 4 rows per block of 320 lanes; each lane of a pair computes half
 // of the row's phases (all its OPD loads issued first) and shares them with its partner.  The intermediate is
@@ -31,11 +34,12 @@
 // (each lane owns its 20 outputs), then one read-modify-write of the accumulator per call, 16 bytes
 // (the block's 4 columns) per row, the 8 blocks of a 32-column group (one 128-byte line of every
 // accumulator row) launched 8 apart, so that the dispatcher places them on one XCD and its L2 merges
-// their writes; the on-axis sample of each frame is the Strehl ratio.  With at most 96 registers 3 blocks
-// share a CU.  With more (the sums in registers: 124) only 2 do, because a CU takes 5-wavefront blocks only
-// while every SIMD has room for 2 more of their wavefronts: 0.81 to 0.85 instead of 0.71 ms, and as much with 3
-// barriers a frame (transposes of complex values) as with 4.
-// 9 stars x 20 frames: 1.07 ms for both passes (traced: rows 0.56 ms, at 4.1 TB/s; columns 0.71 ms).  The rows are
+// their writes; the on-axis sample of each frame is the Strehl ratio.  With an 80-register target 3 blocks
+// share a CU (at 96 they fit too, but not after every order in which blocks end).  With more (the sums in
+// registers: 124) only 2 do, because a CU takes 5-wavefront blocks only while every SIMD has room for 2 more of
+// their wavefronts: 0.81 to 0.85 instead of 0.71 ms, and as much with 3 barriers a frame (transposes of complex
+// values) as with 4.
+// 9 stars x 20 frames: 1.07 to 1.09 ms for both passes (traced: rows 0.56 ms, at 4.1 TB/s; columns 0.71 ms).  The rows are
 // bound by HBM; the columns by issue (with the reads taken out they took 0.66 ms, the reads alone 0.44).
 // 1.51 ms with T in column blocks of 8, one row or column per 80 consecutive lanes and each lane reading its
 // column with 64-byte strides.
@@ -97,10 +101,13 @@ __device__ __forceinline__ void lane_place(int tid, int& q, int& h, int& line) {
   line = (tid >> 4) & 3;
 }
 
-// Four-step twiddles W_M^(n2 k1) of lane (n2 = q, h), k1 = 2k + h: exact every 4 steps, products of
-// W_M^(2 n2) between.
+// First register of a lane pair's odd lane whose index k or t = j + 2 h wraps round to j + 2 h - 20.
+constexpr int kWrap = kNZ - 2;
+
+// Four-step twiddles W_M^(n2 k1) of lane (n2 = q, h), k1 = 2k + h, k = j + 2 h mod 20 in register j: exact every
+// 4 registers and where k wraps, products of W_M^(2 n2) between.
 struct LineTwiddles {
-  float2 start[kNZ / 4], step;
+  float2 start[kNZ / 4], wrap, step;
 };
 __device__ __forceinline__ LineTwiddles line_twiddles(int q, int h) {
   LineTwiddles tw;
@@ -109,9 +116,11 @@ __device__ __forceinline__ LineTwiddles line_twiddles(int q, int h) {
   tw.step = make_float2(__builtin_amdgcn_cosf(sr), __builtin_amdgcn_sinf(sr));
 #pragma unroll
   for (int b = 0; b < kNZ / 4; ++b) {
-    const float rev = -(float)(q * (8 * b + h)) * kInvM;  // q (8 b + h) < M
+    const float rev = -(float)(q * (8 * b + 5 * h)) * kInvM;  // q (8 b + 5 h) < M
     tw.start[b] = make_float2(__builtin_amdgcn_cosf(rev), __builtin_amdgcn_sinf(rev));
   }
+  const float wr = -(float)(q * (h ? 1 : 2 * kWrap)) * kInvM;
+  tw.wrap = make_float2(__builtin_amdgcn_cosf(wr), __builtin_amdgcn_sinf(wr));
   return tw;
 }
 
@@ -127,7 +136,7 @@ __device__ __forceinline__ void line_transform(const float2 (&v)[kNZ], float2 (&
   for (int n1 = 0; n1 < kNZ; ++n1) z[n1] = v[n1];
   if (h) {  // lanes with odd outputs
 #pragma unroll
-    for (int n1 = 0; n1 < kNZ; ++n1) z[n1] = twiddle_mul<kQ, -1>(z[n1], n1);
+    for (int n1 = 0; n1 < kNZ; ++n1) z[n1] = twiddle_mul<8, -1>(z[n1], n1);
   }
   RegFFT<kNZ, -1>::run(z);
   // four-step twiddle W_M^(n2 k1), k1 = 2k + h
@@ -140,31 +149,37 @@ __device__ __forceinline__ void line_transform(const float2 (&v)[kNZ], float2 (&
       float2 t = tw.start[b];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
+        if (4 * b + e == kWrap) t = tw.wrap;
         z[4 * b + e] = cmul(z[4 * b + e], t);
         t = cmul(t, step);
       }
     }
   }
-  // transpose: lane (n2, h) holds Y[2k + h]; lane (k1, h) takes samples n2 = 2t + h
-  float* wr = pl + plane_at(h, q);        // row 2k + h is 84 k further on
-  const float* rd = pl + plane_at(q, h);  // column 2t + h is 4 t further on
+  // transpose: lane (n2, h) holds Y[2k + h]; lane (k1, h) takes samples n2 = 2t + h; k and t are j + 2 h mod 20
+  float* wr = pl + plane_at(h, q) + 2 * 84 * h;           // row 2k + h is 84 k further on
+  const float* rd = pl + plane_at(q, h) + 2 * 4 * h;      // column 2t + h is 4 t further on
+  int hh = h;  // opaque: in a loop over frames the two are formed again rather than kept
+  asm volatile("" : "+v"(hh));
+  float* wr_wrap = wr - kNZ * 84 * hh;
+  const float* rd_wrap = rd - kNZ * 4 * hh;
 #pragma unroll
-  for (int k = 0; k < kNZ; ++k) wr[84 * k] = z[k].x;
+  for (int k = 0; k < kNZ; ++k) (k < kWrap ? wr : wr_wrap)[84 * k] = z[k].x;
   __syncthreads();
 #pragma unroll
-  for (int t = 0; t < kNZ; ++t) x[t].x = rd[4 * t];
+  for (int t = 0; t < kNZ; ++t) x[t].x = (t < kWrap ? rd : rd_wrap)[4 * t];
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < kNZ; ++k) wr[84 * k] = z[k].y;
+  for (int k = 0; k < kNZ; ++k) (k < kWrap ? wr : wr_wrap)[84 * k] = z[k].y;
   __syncthreads();
 #pragma unroll
-  for (int t = 0; t < kNZ; ++t) x[t].y = rd[4 * t];
+  for (int t = 0; t < kNZ; ++t) x[t].y = (t < kWrap ? rd : rd_wrap)[4 * t];
   __syncthreads();
   moved();
   RegFFT<kNZ, -1>::run(x);
+  __builtin_amdgcn_sched_barrier(0);  // the products below, moved up into the transform, cost registers
   if (h) {
 #pragma unroll
-    for (int c = 0; c < kNZ; ++c) x[c] = twiddle_mul<kQ, -1>(x[c], c);
+    for (int c = 0; c < kNZ; ++c) x[c] = twiddle_mul<8, -1>(x[c], c);
   }
   // h = 0: X[c] = E + W O (partner holds W O); h = 1: X[c + 20] = E (partner) - W O, one fused operation
   // by the lane's sign for both
@@ -240,7 +255,7 @@ __global__ __launch_bounds__(kLines * kP) void psf_rows_kernel(const PsfLaunch a
 // Column pass.  Block b = 64 j + 8 m + x takes columns 4 m .. 4 m + 3 of the 32-column group
 // g = 8 j + x (groups past the last one leave at once).
 template <bool FULL>
-__global__ __launch_bounds__(kLines * kP) __attribute__((amdgpu_waves_per_eu(5))) void psf_cols_kernel(const PsfLaunch a, int64_t f0, int nf,
+__global__ __launch_bounds__(kLines * kP) __attribute__((amdgpu_waves_per_eu(6))) void psf_cols_kernel(const PsfLaunch a, int64_t f0, int nf,
                                                                int n_groups, const float2* __restrict__ T,
                                                                float* __restrict__ acc, float* __restrict__ strehl) {
   // the transposes' planes; before them each wavefront's part of the columns of a frame

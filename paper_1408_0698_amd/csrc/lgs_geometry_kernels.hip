@@ -53,8 +53,8 @@ __device__ __forceinline__ double lane_f64(double v, int r) {
 // One wavefront: kProjRows rows of kProjCols tiles of 64 columns of one target's pupil.  The screen
 // coordinates of a layer are affine in the pupil indices, X = ax + b (j + 1/2 - N/2) and Y likewise, so
 // the column part of a lane serves all its rows, and the row part is uniform (lane r works it out
-// for row r) and serves all tiles.  Where the footprint takes at most one sample per pixel (b <= 1: the
-// cone shrinks it, and screens are rarely finer than the pupil), the screen row above a pupil row's
+// for row r) and serves all tiles.  Where a wavefront's rows go on by at most one sample (the cone shrinks
+// the footprint, and screens are rarely finer than the pupil), the screen row above a pupil row's
 // point is the one above or below the previous row's point, so each row costs one new screen row;
 // otherwise the rows above are read too.  Positions, weights and sums are FP64, FP32 out.
 // Bound by FP64 issue (290 VALU instructions per lane for its 8 pixels through three layers, 4.6
@@ -89,7 +89,11 @@ __global__ __launch_bounds__(64 * kProjWaves) void project_layers_kernel(const P
     int iy[kProjRows];
 #pragma unroll
     for (int r = 0; r < kProjRows; ++r) iy[r] = lane_i32(iyv, r);
-    const bool shared = m.b <= 1.0;  // uniform
+    // rows that go on by one sample at most (uniform).  Told by the steps and not by b <= 1: where Y passes a
+    // power of two its rounding changes, and with b = 1 the row may then go on by two
+    bool shared = true;
+#pragma unroll
+    for (int r = 1; r < kProjRows; ++r) shared = shared && iy[r] - iy[r - 1] <= 1;
     // the reads of every tile and row first
     Pair top[kProjCols], bot[kProjCols][kProjRows];
     double fx[kProjCols];

@@ -447,10 +447,13 @@ def polychromatic_psf(plans, weights, opd, out, strehl=None, stream=None):
     return out
 
 
-def _doubles(values):
-    """double C array of a list of numbers (array() copies a list several times faster than ctypes)."""
-    a = array("d", [float(v) for v in values] or [0.0])
-    return (C.c_double * len(a)).from_buffer(a)
+def _doubles(values, n):
+    """double C array of n numbers (the rest 0; IndexError for more than n).  array() copies a list several
+    times faster than ctypes' own element loop, which takes the lists of another length."""
+    values = [float(v) for v in values]
+    if n > 0 and len(values) == n:
+        return (C.c_double * n).from_buffer(array("d", values))
+    return (C.c_double * n)(*values)
 
 
 def _layer_args(layers):
@@ -468,13 +471,13 @@ def _layer_args(layers):
         pitch.append(stride[0])
         par += l[1:5]
     return (n, (C.c_void_p * n)(*ptrs), (C.c_int32 * n)(*rows), (C.c_int32 * n)(*cols), (C.c_int64 * n)(*pitch),
-            _doubles(par))
+            _doubles(par, 4 * n))
 
 
 def project_layers(layers, pupil_n, dx_m, targets, out, tilt=None, stream=None):
     """Cone-effect open-loop wavefronts: targets = [(theta_x, theta_y, altitude_m or 0)], out float32 [T][N][N]."""
     n, ptrs, rows, cols, pitch, par = _layer_args(layers)
-    tp = _doubles(chain.from_iterable(targets))
+    tp = _doubles(chain.from_iterable(targets), 3 * max(1, len(targets)))
     if out.dim() != 3 or out.stride(2) != 1:
         raise ValueError("out must be [targets][rows][cols] with contiguous rows")
     _check(_lib.shw_project_layers(n, ptrs, rows, cols, pitch, par, pupil_n, dx_m, len(targets), tp, _ptr(tilt),
@@ -485,7 +488,7 @@ def project_layers(layers, pupil_n, dx_m, targets, out, tilt=None, stream=None):
 def uplink_tilt(layers, lgs, llt_diameter_m, n_samples, out, stream=None):
     """lgs = [(launch_x_m, launch_y_m, theta_x, theta_y, sodium_altitude_m)]; out float64 device [n][2] radians."""
     n, ptrs, rows, cols, pitch, par = _layer_args(layers)
-    lp = _doubles(chain.from_iterable(lgs))
+    lp = _doubles(chain.from_iterable(lgs), 5 * max(1, len(lgs)))
     _check(_lib.shw_uplink_tilt(n, ptrs, rows, cols, pitch, par, len(lgs), lp, llt_diameter_m, n_samples, _ptr(out),
                                 _stream_ptr(stream)), "shw_uplink_tilt")
     return out

@@ -37,6 +37,7 @@ struct ResidualLaunch {
   int32_t streaming;        // write the result past the caches
   int64_t out_pitch, out_stride;
   ResidualOut o[kResidualChunk];
+  int64_t rows;             // pupil rows of this launch
 };
 
 hipError_t launch_dm_surface(const DmLaunch& a, const float* coefs, float* surf, hipStream_t st);

@@ -126,7 +126,7 @@ __global__ __launch_bounds__(256) void residual_kernel(const ResidualLaunch a, f
   const int e = tile * 256 + threadIdx.x;
   const int y = e / a.quads;
   const int x = 4 * (e - y * a.quads);
-  if (y >= a.pupil_n) return;
+  if (y >= (int)a.rows) return;
   const int k0 = group * a.per_block;
   const int k1 = min(k0 + a.per_block, a.n_out);
   const int64_t scr = (int64_t)y * a.screen_pitch + x;
@@ -263,17 +263,13 @@ hipError_t launch_dm_surface(const DmLaunch& a, const float* coefs, float* surf,
   return hipGetLastError();
 }
 
-hipError_t launch_residual(ResidualLaunch& a, int n_dm, float* out, hipStream_t st) {
-  a.quads = (a.pupil_n + 3) / 4;
-  const int64_t tiles = ((int64_t)a.quads * a.pupil_n + 255) / 256;
+static hipError_t launch_residual_rows(ResidualLaunch& a, int n_dm, float* out, hipStream_t st) {
+  const int64_t tiles = (a.quads * a.rows + 255) / 256;
   // enough blocks to fill the GPU about twice (8 resident per CU), the rest of the outputs in the
   // blocks' loops
   int64_t pb = (int64_t)a.n_out * tiles / 4096;
   a.per_block = pb < 1 ? 1 : (pb > a.n_out ? a.n_out : (int)pb);
   a.xcd_tiles = (int32_t)((tiles + 7) / 8);
-  // results larger than twice the L2s (8 x 4 MB) leave them before anyone reads them: written past
-  // the caches they leave the screen and the mirrors there (60 outputs of 800^2: 29.3 against 31.3 us)
-  a.streaming = (int64_t)a.n_out * a.pupil_n * a.pupil_n * (int64_t)sizeof(float) > ((int64_t)64 << 20);
   const dim3 grid((unsigned)(8 * a.xcd_tiles * ((a.n_out + a.per_block - 1) / a.per_block)));
   switch (n_dm) {
     case 0: hipLaunchKernelGGL(residual_kernel<0>, grid, dim3(256), 0, st, a, out); break;
@@ -284,6 +280,26 @@ hipError_t launch_residual(ResidualLaunch& a, int n_dm, float* out, hipStream_t 
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+hipError_t launch_residual(ResidualLaunch& a, int n_dm, float* out, hipStream_t st) {
+  a.quads = (a.pupil_n + 3) / 4;
+  // results larger than twice the L2s (8 x 4 MB) leave them before anyone reads them: written past
+  // the caches they leave the screen and the mirrors there (60 outputs of 800^2: 29.3 against 31.3 us)
+  a.streaming = (int64_t)a.n_out * a.pupil_n * a.pupil_n * (int64_t)sizeof(float) > ((int64_t)64 << 20);
+  // the kernel counts quads in 32 bits and a launch has at most 2^32 lanes: pupils above 65536 pixels go in
+  // bands of rows
+  const int64_t band = ((int64_t)1 << 30) / a.quads;
+  for (int64_t y0 = 0; y0 < a.pupil_n; y0 += a.rows) {
+    a.rows = a.pupil_n - y0 < band ? a.pupil_n - y0 : band;
+    const hipError_t e = launch_residual_rows(a, n_dm, out + y0 * a.out_pitch, st);
+    if (e != hipSuccess) return e;
+    // to the next band, and back to the first row after the last one
+    const int64_t step = y0 + a.rows < a.pupil_n ? a.rows : -y0;
+    a.screen += step * a.screen_pitch;
+    for (int d = 0; d < n_dm; ++d) a.surf[d] += step * a.surf_size[d];
+  }
+  return hipSuccess;
 }
 
 }  // namespace shw

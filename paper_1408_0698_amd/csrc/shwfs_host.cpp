@@ -1067,31 +1067,36 @@ extern "C" int shw_residual_opd(const float* d_screen, int32_t screen_rows, int3
     a.surf_size[d] = surf_size[d];
   }
   // outputs with the same mirror windows next to each other (the kernel then reads the mirrors
-  // once for a run of them)
-  std::vector<ResidualOut> outs((size_t)n_out);
-  for (int k = 0; k < n_out; ++k) {
-    ResidualOut& o = outs[k];
-    o = ResidualOut{};
-    o.scr_off = (int64_t)scr_origin[2 * k] * screen_pitch + scr_origin[2 * k + 1];
-    o.out = k;
-    for (int d = 0; d < n_dm; ++d) {
-      const int32_t* w = dm_origin + ((int64_t)k * n_dm + d) * 2;
-      o.dm_off[d] = (int64_t)w[0] * surf_size[d] + w[1];
+  // once for a run of them), in groups of a bounded size, so that nothing here throws
+  constexpr int kGroup = 1024;
+  ResidualOut outs[kGroup];
+  for (int64_t g0 = 0; g0 < n_out; g0 += kGroup) {
+    const int ng = n_out - g0 < kGroup ? (int)(n_out - g0) : kGroup;
+    for (int i = 0; i < ng; ++i) {
+      const int64_t k = g0 + i;
+      ResidualOut& o = outs[i];
+      o = ResidualOut{};
+      o.scr_off = (int64_t)scr_origin[2 * k] * screen_pitch + scr_origin[2 * k + 1];
+      o.out = k;
+      for (int d = 0; d < n_dm; ++d) {
+        const int32_t* w = dm_origin + (k * n_dm + d) * 2;
+        o.dm_off[d] = (int64_t)w[0] * surf_size[d] + w[1];
+      }
     }
-  }
-  std::stable_sort(outs.begin(), outs.end(), [](const ResidualOut& u, const ResidualOut& v) {
-    for (int d = 0; d < kMaxDm; ++d)
-      if (u.dm_off[d] != v.dm_off[d]) return u.dm_off[d] < v.dm_off[d];
-    return false;
-  });
-  // launches of equal size
-  const int launches = (n_out + kResidualChunk - 1) / kResidualChunk;
-  for (int i = 0; i < launches; ++i) {
-    const int k0 = (int)((int64_t)n_out * i / launches), k1 = (int)((int64_t)n_out * (i + 1) / launches);
-    a.n_out = k1 - k0;
-    std::copy(outs.begin() + k0, outs.begin() + k1, a.o);
-    hipError_t e = launch_residual(a, n_dm, d_out, (hipStream_t)stream);
-    if (e != hipSuccess) return hip_fail(e, "shw_residual_opd launch");
+    std::stable_sort(outs, outs + ng, [](const ResidualOut& u, const ResidualOut& v) {
+      for (int d = 0; d < kMaxDm; ++d)
+        if (u.dm_off[d] != v.dm_off[d]) return u.dm_off[d] < v.dm_off[d];
+      return false;
+    });
+    // launches of equal size
+    const int launches = (ng + kResidualChunk - 1) / kResidualChunk;
+    for (int i = 0; i < launches; ++i) {
+      const int k0 = ng * i / launches, k1 = ng * (i + 1) / launches;
+      a.n_out = k1 - k0;
+      std::copy(outs + k0, outs + k1, a.o);
+      hipError_t e = launch_residual(a, n_dm, d_out, (hipStream_t)stream);
+      if (e != hipSuccess) return hip_fail(e, "shw_residual_opd launch");
+    }
   }
   return ok();
 }

@@ -1391,7 +1391,9 @@ extern "C" int shw_wfs_interaction_matrix(shw_wfs_plan* p, const shw_dm_plan* dm
     return fail(SHW_E_UNSUPPORTED, "no calibration kernel for this plan and launch variant");
   const int32_t nb = (dm->patch - 1) / p->npx + 2;
   const int64_t per_mode = (int64_t)p->n_wfs * nb * nb;
-  if (nb >= p->cfg.n_subap || per_mode >= ((int64_t)1 << 30))
+  // pairs per launch: 80 lanes each, and a launch has fewer than 2^32
+  constexpr int64_t kMaxPairs = (int64_t)1 << 25;
+  if (nb >= p->cfg.n_subap || per_mode > kMaxPairs)
     return fail(SHW_E_UNSUPPORTED, "an influence function reaches the whole pupil");
   ModesLaunch q{};
   q.a = base_launch(p);
@@ -1415,7 +1417,7 @@ extern "C" int shw_wfs_interaction_matrix(shw_wfs_plan* p, const shw_dm_plan* dm
   hipStream_t st = (hipStream_t)stream;
   // the difference of equal slopes times the scale (0 for any finite scale)
   hipError_t e = launch_fill_matrix(d_im, (int64_t)p->n_wfs * 2 * p->n_valid, n_modes, ld_im, 0.0f * scale, st);
-  const int64_t fit = (((int64_t)1 << 31) - 8) / per_mode;  // pair numbers stay below 2^31
+  const int64_t fit = kMaxPairs / per_mode;
   const int32_t chunk = fit < kModesChunk ? (int32_t)fit : kModesChunk;
   for (int32_t m0 = 0; m0 < n_modes && e == hipSuccess; m0 += chunk) {
     q.n_modes = n_modes - m0 < chunk ? n_modes - m0 : chunk;

@@ -236,9 +236,16 @@ __global__ __launch_bounds__(256) void fill_matrix_kernel(float* __restrict__ im
 
 hipError_t launch_fill_matrix(float* im, int64_t rows, int32_t cols, int64_t ld, float v, hipStream_t st) {
   const int32_t rq = (cols + 3) / 4;
-  const int64_t quads = rows * rq;
-  hipLaunchKernelGGL(fill_matrix_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, st, im, quads, rq, cols, ld, v);
-  return hipGetLastError();
+  // rows per launch: fewer than the 2^32 lanes that one may have
+  const int64_t band = ((int64_t)1 << 31) / rq;
+  for (int64_t r0 = 0; r0 < rows; r0 += band) {
+    const int64_t quads = (rows - r0 < band ? rows - r0 : band) * rq;
+    hipLaunchKernelGGL(fill_matrix_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, st, im + r0 * ld, quads, rq,
+                       cols, ld, v);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_influence_opd(const InfluenceLaunch& a, float* out, hipStream_t st) {

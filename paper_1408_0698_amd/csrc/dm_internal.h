@@ -18,6 +18,12 @@ struct DmLaunch {
   float inv_2s2;     // 1 / (2 sigma^2)
 };
 
+// Influence function (times amp) at (dx, dy) pixels from its actuator.  The sum of squares is written out as
+// one fused operation: the frames of shw_dm_influence_opd and the calibration kernel's own samples are the same bits.
+__device__ __forceinline__ float influence(float amp, float dx, float dy, float inv_2s2) {
+  return amp * expf(-fmaf(dx, dx, dy * dy) * inv_2s2);
+}
+
 // One residual output: element offsets of its windows' first pixels and its place in the result.
 struct ResidualOut {
   int64_t scr_off;

@@ -191,7 +191,7 @@ __global__ __launch_bounds__(256) void influence_kernel(const InfluenceLaunch a,
   if (j >= cx - a.half_patch && j < cx + a.half_patch && i >= cy - a.half_patch && i < cy + a.half_patch) {
     const float dx = (float)j + 0.5f - (float)half - ax;
     const float dy = (float)i + 0.5f - (float)half - ay;
-    v = a.amp[k] * expf(-(dx * dx + dy * dy) * a.inv_2s2);
+    v = influence(a.amp[k], dx, dy, a.inv_2s2);
   }
   out[(int64_t)k * a.out_stride + (int64_t)y * a.out_pitch + x] = v;
 }

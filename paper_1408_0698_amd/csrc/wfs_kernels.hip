@@ -45,6 +45,7 @@
 #include <hip/hip_runtime.h>
 
 #include "band_rebin.h"
+#include "dm_internal.h"
 #include "internal.h"
 #include "noise.h"
 #include "regfft.h"
@@ -497,7 +498,7 @@ __device__ __forceinline__ void wfs_fused_group(const WfsLaunch& a, int64_t grou
         const int j = pj + x;
         const float dx = (float)j + 0.5f - (float)q.half - mode.ax;
         const bool in = in_y && j >= cx - q.half_patch && j < cx + q.half_patch;
-        ov[x] = in ? amp * expf(-(dx * dx + dy * dy) * q.inv_2s2) : 0.0f;
+        ov[x] = in ? influence(amp, dx, dy, q.inv_2s2) : 0.0f;
       }
     } else {
 #pragma unroll

@@ -391,7 +391,7 @@ int shw_psf_plan_destroy(shw_psf_plan* plan);
  *   d_ee[s*n_r + k] = sum of P over pixels (v, u) with (u - M/2)^2 + (v - M/2)^2 <= r^2
  *                     divided by the sum of P over the whole array
  * (FP64 sums in a fixed order: the same inputs give the same result).  M <=
- * 4096 (SHW_E_UNSUPPORTED otherwise).  The plan keeps a workspace of n_psf *
+ * 2048 (SHW_E_UNSUPPORTED otherwise).  The plan keeps a workspace of n_psf *
  * 200 * (n_r + 1) doubles; growing it synchronises the device.  Asynchronous
  * otherwise; calls on one plan must not overlap.
  */

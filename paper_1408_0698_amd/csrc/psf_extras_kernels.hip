@@ -36,7 +36,7 @@ __device__ __forceinline__ int isqrt_floor(double q) {
 // Bound by the read: 9 PSFs of 1600^2 (92 MB) take 21 us traced = 4.4 TB/s; a wavefront per single row,
 // staged in LDS and scanned whole, took 52 us.
 constexpr int kEeWaves = 4;
-constexpr int kEeSteps = 8;  // 256-pixel steps per half row: M <= 4096
+constexpr int kEeSteps = 4;  // 256-pixel steps that cover a folded half row: M <= 2048
 static_assert(kMaxRadii <= 64, "one lane per radius");
 
 // Pixels p .. p + 3 (16 bytes at 4-byte alignment).
@@ -52,8 +52,6 @@ __device__ __forceinline__ double ee_scan(double v, int lane) {
   return v;
 }
 
-// STEPS 256-pixel steps cover the folded half row (STEPS x 256 >= H).
-template <int STEPS>
 __global__ __launch_bounds__(64 * kEeWaves) void ee_rows_kernel(const EeLaunch a) {
   extern __shared__ __align__(16) double ee_pre[];  // [wavefront][H rounded up to 4]
   __shared__ double fin[kEeWaves][kMaxRadii + 1];
@@ -72,9 +70,9 @@ __global__ __launch_bounds__(64 * kEeWaves) void ee_rows_kernel(const EeLaunch a
     const bool pair = dv > 0 && c + dv < M;
     const float* hi = P + (int64_t)(c + dv < M ? c + dv : c - dv) * M;
     const float* lo = P + (int64_t)(c - dv) * M;
-    EeQuad q[STEPS][4];
+    EeQuad q[kEeSteps][4];
 #pragma unroll
-    for (int i = 0; i < STEPS; ++i) {
+    for (int i = 0; i < kEeSteps; ++i) {
       const int j = 256 * i + 4 * lane;
 #pragma unroll
       for (int k = 0; k < 4; ++k) q[i][k] = EeQuad{0.0f, 0.0f, 0.0f, 0.0f};
@@ -102,7 +100,7 @@ __global__ __launch_bounds__(64 * kEeWaves) void ee_rows_kernel(const EeLaunch a
     for (int u = c - (H > 0 ? H : 1); u >= 0; --u) single(u);
     double carry = 0.0;
 #pragma unroll
-    for (int i = 0; i < STEPS; ++i) {
+    for (int i = 0; i < kEeSteps; ++i) {
       double p[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
@@ -172,12 +170,8 @@ hipError_t launch_encircled_energy(const EeLaunch& a, hipStream_t st) {
   const int h = (a.m - c < c + 1 ? a.m - c : c + 1) & ~3;
   const size_t lds = (size_t)kEeWaves * h * sizeof(double);
   const dim3 grid(kEeGroups, (unsigned)a.n_psf);
-  if (h <= 4 * 256)
-    hipLaunchKernelGGL(ee_rows_kernel<4>, grid, dim3(64 * kEeWaves), lds, st, a);
-  else if (h <= kEeSteps * 256)
-    hipLaunchKernelGGL(ee_rows_kernel<kEeSteps>, grid, dim3(64 * kEeWaves), lds, st, a);
-  else
-    return hipErrorInvalidValue;
+  if (h > kEeSteps * 256) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(ee_rows_kernel, grid, dim3(64 * kEeWaves), lds, st, a);
   hipLaunchKernelGGL(ee_final_kernel, dim3((unsigned)a.n_psf), dim3(64 * kEeFinalWaves), 0, st, a);
   return hipGetLastError();
 }

@@ -1645,7 +1645,7 @@ static int ee_setup(const shw_psf_plan* plan, const float* d_psf, int32_t n_psf,
   a = EeLaunch{};
   if (!plan) return fail(SHW_E_INVALID, "plan is NULL");
   const int M = plan->fft_m;
-  if (M > 4096) return fail(SHW_E_UNSUPPORTED, "encircled energy supports fft_m <= 4096");
+  if (M > 2048) return fail(SHW_E_UNSUPPORTED, "encircled energy supports fft_m <= 2048");
   if (n_psf < 0) return fail(SHW_E_INVALID, "n_psf < 0");
   if (n_psf == 0) return ok();
   if (!d_psf || !r_px || !d_ee) return fail(SHW_E_INVALID, "NULL argument");

@@ -268,8 +268,15 @@ int shw_wfs_plan_destroy(shw_wfs_plan* plan);
  * fused kernel with the second kernel's code (inversion head 4: the same
  * images and slopes as 12 at that head) and keeps no detector workspace.
  * New plans start on the fastest measured variant: 13 for band-limited
- * 40-point shapes, 9 for the other 40-point shapes, 4 for band-limited
+ * 40-point shapes, for the other 40-point shapes 9 up to 4096 valid
+ * sub-apertures a frame (all sensors) and 8 above, 4 for band-limited
  * sodium plans, 2 for the other sodium plans, 0 otherwise.
+ * Plans of 8-pixel NGS sub-apertures (fft_n = conv_n = 16, det_n 8 or 16)
+ * without noise and without a threshold run none of the variants: their
+ * slopes come from the line moments of the field, whatever the variant.
+ * set_variant, get_variant and variant_params answer for them as for other
+ * plans, autotune times the same launch for each variant, and a figure
+ * recorded with variant_params is not of the kernel that they describe.
  * shw_wfs_plan_autotune times every variant on the given inputs
  * (reps launches each after two warm-up launches, HIP events on the stream;
  * synchronous), selects the fastest, except that the plan's starting variant
@@ -560,7 +567,8 @@ int shw_push_pull(const float* d_slopes, int32_t n_modes, int32_t n_slopes, floa
  * m < n_modes.  (row0, col0): the pupil's window of the surface, SHW_E_INVALID if it leaves it.
  * SHW_E_UNSUPPORTED, with nothing launched, for plans with noise, sodium sub-layers or a precision
  * form, shapes other than 10-pixel sub-apertures with fft_n = conv_n = 40 and det_n = 16, launch
- * variants other than 13, and patches that reach across the whole pupil.  Asynchronous.
+ * variants other than 13 (set or found by autotuning: such plans are calibrated by whole frames), and
+ * patches that reach across the whole pupil or 2^25 sub-apertures of all sensors.  Asynchronous.
  */
 int shw_wfs_interaction_matrix(shw_wfs_plan* plan, const shw_dm_plan* dm, const int32_t* acts, int32_t n_modes,
                                float amplitude_m, int32_t row0, int32_t col0, float scale, float* d_im,

@@ -32,7 +32,10 @@ struct LayerSet {
 // sum over layers of the bilinear screen sample at (1 - h/H) r + h theta, H the source altitude
 // (0: infinity), plus tilt[t] . r when tilt is set.  In screen samples that point is
 // (ax + b (j + 1/2 - N/2), ay + b (i + 1/2 - N/2)), with a map for each target and layer.
-constexpr int kProjectMaps = 120;  // maps per launch (they travel in the arguments)
+// Where a call's maps fit one launch they travel in its arguments; a call of more maps hands over what they are
+// made of instead, and the kernel makes them (the same bits).
+constexpr int kProjectMaps = 120;    // maps per launch
+constexpr int kProjectTargets = 93;  // targets per launch of the second form
 struct ProjectLayer {
   const float* screen;
   int64_t pitch;
@@ -41,16 +44,35 @@ struct ProjectLayer {
 struct ProjectMap {
   double ax, ay, b;
 };
+struct ProjectPlace {
+  double x0, y0;       // origin, screen samples
+  double alt_m, h;     // altitude, metres and screen samples
+  double inv_pitch;    // 1 / sample spacing
+};
+struct ProjectTarget {
+  double theta_x, theta_y, inv_h;
+};
 struct ProjectLaunch {
   ProjectLayer layer[kMaxLayers];
-  ProjectMap map[kProjectMaps];  // [n_t][n_layers]
+  union {
+    ProjectMap map[kProjectMaps];  // [n_t][n_layers]
+    struct {
+      ProjectPlace place[kMaxLayers];
+      ProjectTarget target[kProjectTargets];
+    };
+  };
   int32_t n_layers, n_t, pupil_n, pad0;
   double dx;
   const double* tilt;            // nullable [n_t][2] radians, already offset to the chunk
   float* out;                    // target t at out + t * out_stride
   int64_t out_pitch, out_stride;
 };
-hipError_t launch_project_layers(const ProjectLaunch& a, hipStream_t st);
+// The map of a target on a layer, as on the host.
+__host__ __device__ inline ProjectMap project_map(const ProjectPlace& L, const ProjectTarget& g, double dx) {
+#pragma clang fp contract(off)
+  return ProjectMap{L.x0 + L.h * g.theta_x, L.y0 + L.h * g.theta_y, (1.0 - L.alt_m * g.inv_h) * dx * L.inv_pitch};
+}
+hipError_t launch_project_layers(const ProjectLaunch& a, bool maps, hipStream_t st);
 
 // Uplink tilt of LGS k: least-squares tilt of the summed layer OPD over the launch telescope's
 // beam, an n_s x n_s grid of samples inside the disc of diameter d, the beam centred at

@@ -62,6 +62,11 @@ __device__ __forceinline__ double lane_f64(double v, int r) {
 // 108 us with one lane per pixel, its own row arithmetic, a division by the sample spacing per layer
 // and the layers padded to groups of four.  4 x 1 and 8 x 2 rows x tiles per wavefront: 43 and 48 us;
 // tiles of the screen staged in LDS: 55 us (two barriers per layer).
+// MAPS: the maps come ready in the arguments, else the kernel makes them (6 more FP64 instructions a layer:
+// 1-4 % where one launch does either way).  The line is at one launch: the maps of 18 targets of 800^2 through
+// seven layers take two, 77 instead of 70 us; 18 of 200^2 through 16 layers take three, 52 instead of 25 us, the
+// serial chain of 16 layers each time; 40 of 130^2 through 16 layers six, 98 instead of 24 us.
+template <bool MAPS>
 __global__ __launch_bounds__(64 * kProjWaves) void project_layers_kernel(const ProjectLaunch a) {
   // consecutive blocks go to the 8 XCDs in turn: XCD c takes the tile rows c mod 8, all targets of a
   // tile before the next one, because the targets' footprints on a layer largely overlap
@@ -74,7 +79,6 @@ __global__ __launch_bounds__(64 * kProjWaves) void project_layers_kernel(const P
   const int j0 = blockIdx.z * 64, jstep = gridDim.z * 64;  // tile c starts at column j0 + c jstep
   const double centre = 0.5 - 0.5 * n;
   const double ic = (double)min(i0 + (lane & (kProjRows - 1)), n - 1) + centre;
-  const ProjectMap* map = a.map + t * a.n_layers;
   double acc[kProjCols][kProjRows];
 #pragma unroll
   for (int c = 0; c < kProjCols; ++c)
@@ -82,7 +86,7 @@ __global__ __launch_bounds__(64 * kProjWaves) void project_layers_kernel(const P
     for (int r = 0; r < kProjRows; ++r) acc[c][r] = 0.0;
   for (int l = 0; l < a.n_layers; ++l) {
     const ProjectLayer& L = a.layer[l];
-    const ProjectMap m = map[l];
+    const ProjectMap m = MAPS ? a.map[t * a.n_layers + l] : project_map(a.place[l], a.target[t], a.dx);
     double fyv;
     const int iyv = split_coord(fma(m.b, ic, m.ay), L.rows, fyv);
     const double gyv = 1.0 - fyv;
@@ -156,11 +160,14 @@ __global__ __launch_bounds__(64 * kProjWaves) void project_layers_kernel(const P
   }
 }
 
-hipError_t launch_project_layers(const ProjectLaunch& a, hipStream_t st) {
+hipError_t launch_project_layers(const ProjectLaunch& a, bool maps, hipStream_t st) {
   constexpr int k8 = 8 * kRows;
   const int tiles = (a.pupil_n + 63) / 64;
   const dim3 grid(8u * (unsigned)a.n_t, (unsigned)((a.pupil_n + k8 - 1) / k8), (unsigned)((tiles + kProjCols - 1) / kProjCols));
-  hipLaunchKernelGGL(project_layers_kernel, grid, dim3(64 * kProjWaves), 0, st, a);
+  if (maps)
+    hipLaunchKernelGGL(project_layers_kernel<true>, grid, dim3(64 * kProjWaves), 0, st, a);
+  else
+    hipLaunchKernelGGL(project_layers_kernel<false>, grid, dim3(64 * kProjWaves), 0, st, a);
   return hipGetLastError();
 }
 

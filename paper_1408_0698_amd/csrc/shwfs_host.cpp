@@ -1573,23 +1573,25 @@ extern "C" int shw_project_layers(int32_t n_layers, const float* const* d_screen
   a.out_pitch = out_pitch;
   a.out_stride = out_stride;
   hipStream_t st = (hipStream_t)stream;
-  const int chunk = kProjectMaps / n_layers;
-  for (int t0 = 0; t0 < n_targets; t0 += chunk) {
-    const int nt = n_targets - t0 < chunk ? n_targets - t0 : chunk;
-    a.n_t = nt;
-    for (int k = 0; k < nt; ++k) {
+  ProjectPlace place[kMaxLayers];
+  for (int l = 0; l < n_layers; ++l) {
+    const LayerDesc& L = S.layer[l];
+    place[l] = ProjectPlace{L.x0, L.y0, L.alt_m, L.alt_m * L.inv_pitch, L.inv_pitch};
+  }
+  const bool maps = n_targets <= kProjectMaps / n_layers;
+  if (!maps) std::copy(place, place + n_layers, a.place);
+  for (int t0 = 0; t0 < n_targets; t0 += a.n_t) {
+    const int limit = maps ? n_targets : kProjectTargets;
+    a.n_t = n_targets - t0 < limit ? n_targets - t0 : limit;
+    for (int k = 0; k < a.n_t; ++k) {
       const double* q = target_params + 3 * (t0 + k);
-      const double inv_h = q[2] > 0 ? 1.0 / q[2] : 0.0;
-      for (int l = 0; l < n_layers; ++l) {
-        const LayerDesc& L = S.layer[l];
-        const double h = L.alt_m * L.inv_pitch;
-        a.map[k * n_layers + l] = ProjectMap{L.x0 + h * q[0], L.y0 + h * q[1],
-                                             (1.0 - L.alt_m * inv_h) * dx_m * L.inv_pitch};
-      }
+      const ProjectTarget g{q[0], q[1], q[2] > 0 ? 1.0 / q[2] : 0.0};
+      if (!maps) a.target[k] = g;
+      for (int l = 0; maps && l < n_layers; ++l) a.map[k * n_layers + l] = project_map(place[l], g, dx_m);
     }
     a.tilt = d_tilt ? d_tilt + 2 * t0 : nullptr;
     a.out = d_out + t0 * out_stride;
-    hipError_t he = launch_project_layers(a, st);
+    hipError_t he = launch_project_layers(a, maps, st);
     if (he != hipSuccess) return hip_fail(he, "project layers");
   }
   return ok();

@@ -448,12 +448,15 @@ def polychromatic_psf(plans, weights, opd, out, strehl=None, stream=None):
 
 
 def _doubles(values, n):
-    """double C array of n numbers (the rest 0; IndexError for more than n).  array() copies a list several
-    times faster than ctypes' own element loop, which takes the lists of another length."""
-    values = [float(v) for v in values]
+    """double C array of n numbers (the rest 0; IndexError for more than n).  array() converts a whole list at
+    once; lists of another length and what it refuses go through float() and ctypes' own element loop."""
+    values = list(values)
     if n > 0 and len(values) == n:
-        return (C.c_double * n).from_buffer(array("d", values))
-    return (C.c_double * n)(*values)
+        try:
+            return (C.c_double * n).from_buffer(array("d", values))
+        except TypeError:
+            pass
+    return (C.c_double * n)(*[float(v) for v in values])
 
 
 def _layer_args(layers):

@@ -66,3 +66,15 @@ def test_too_many_parameters_are_refused(calls):
     with pytest.raises(IndexError):
         _uplink([(1, 2, 3, 4, 5, 6)])
     assert not calls
+
+
+def test_numbers_of_every_kind(calls):
+    """Whatever float() takes: integers, numpy and torch scalars, texts."""
+    import numpy as np
+    _project([(1, np.float32(2.5), torch.tensor(3.0))])
+    _project([(np.int64(1), "2.5", True)])
+    assert [list(c[1][9]) for c in calls] == [[1, 2.5, 3], [1, 2.5, 1]]
+    with pytest.raises(TypeError):
+        _project([(1, 2, None)])
+    with pytest.raises(ValueError):
+        _project([(1, 2, "high")])

@@ -3,10 +3,14 @@
 Each mode (the influence function of one DM actuator) is pushed and pulled
 by +/- amplitude on the pupil, every sensor of the plan measures both
 frames, and the interaction-matrix column is (s+ - s-) / (2 amplitude).
-All steps are library kernels: influence-function OPD frames, the fused
+All steps are library kernels.  Noise-free plans of the 40-point LGS shape in
+its starting launch variant are calibrated directly: only the sub-apertures
+that a mode's patch reaches are measured, the rest of the matrix is zero.  Any
+other plan (noise, another shape, a launch variant set by hand or found by
+autotuning) takes whole frames: influence-function OPD frames, the fused
 measurement (one launch per chunk of modes, every sensor of the plan
 seeing the same pupil OPD through a zero sensor stride), and the
-push-pull combination into the matrix.
+push-pull combination into the matrix; the same bits, some 2 to 60 times as long.
 """
 from __future__ import annotations
 

@@ -202,7 +202,8 @@ __device__ __forceinline__ void detect_item(const BigLaunch& a, int64_t item0, i
     const int pix = p * dn + q;
     const float* col = jr + (int64_t)q * b * dn + p;
     // b = 512 / det_n is a power of two: from b = 32 on 32 loads in flight per step, for 8 and 16 eight
-    // (partial sums in the same fixed order), not one load per dependent addition
+    // (partial sums in the same fixed order), not one load per dependent addition.  48 items with b = 32: 7.4 us
+    // traced, 7.7 with eight at a time; of the three kernels' 57 us that is within the calls' spread
     float det = 0.0f;
     if (b >= 8) {
       float ps[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};

@@ -34,7 +34,8 @@
 //
 // Bound by issue: matrix and other vector instructions of a SIMD hardly overlap (8 products and 32 FMAs a
 // wavefront take 0.89 of the sum of their times), and the BF16X3 form has 31 + 35 us of them in a frame of
-// six sensors with 4928 sub-apertures.  It takes 71 us traced; plain BF16 and FP16X3 47 and 89 us with the
+// six sensors with 4928 sub-apertures.  It takes 65 us traced (69 to 72 in the first calls of a run, before the
+// card settles); plain BF16 and FP16X3 47 and 89 us with the
 // noise stage (no noise drawn), 61 and 108 us when K^ came from its 21 x 40 form, of whose lines a quarter is
 // in the band, one masked value at a time (BF16X3: 77 and 83 us).  A persistent grid is slower (75-84 us).
 #include <hip/hip_runtime.h>

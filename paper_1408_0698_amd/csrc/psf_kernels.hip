@@ -39,7 +39,9 @@
 // registers: 124) only 2 do, because a CU takes 5-wavefront blocks only while every SIMD has room for 2 more of
 // their wavefronts: 0.81 to 0.85 instead of 0.71 ms, and as much with 3 barriers a frame (transposes of complex
 // values) as with 4.
-// 9 stars x 20 frames: 1.07 to 1.09 ms for both passes (traced: rows 0.56 ms, at 4.1 TB/s; columns 0.71 ms).  The rows are
+// 9 stars x 20 frames: 1.07 to 1.10 ms for both passes back to back, traced 0.50 ms for the rows (4.6 TB/s) and 0.61 for the
+// columns once the card has run them for some 0.2 s.  Before that it is slower: the first 20 calls of a run average
+// 0.56 and 0.70 ms, and the other traced times here are such averages.  The rows are
 // bound by HBM; the columns by issue (with the reads taken out they took 0.66 ms, the reads alone 0.44).
 // 1.51 ms with T in column blocks of 8, one row or column per 80 consecutive lanes and each lane reading its
 // column with 64-byte strides.

@@ -1099,9 +1099,10 @@ __global__ __launch_bounds__(SPB * CONV_N) __attribute__((amdgpu_waves_per_eu(WP
 
 // Push-pull calibration with the code of launch variant 13 (noise off): one block per 4 pairs, the
 // wavefronts formed in the row pass, the slope differences written to the matrix.  Bound by VALU
-// issue like the frames: 256 modes of one 80 x 80 sensor (64 cells each, 16,384 pairs) take 70 us traced,
-// and the matrix's zeros 4 us; influence frames of the whole pupil, their measurement in all 4928
-// sub-apertures and the combination took 4.3 ms for the same bits.
+// issue like the frames: 256 modes of one 80 x 80 sensor (64 cells each, 16,384 pairs) take 62 us traced (68 to 71
+// in the first calls of a run, before the card settles) and the matrix's zeros 5 us, back to back 65 to 66 us for
+// both; influence frames of the whole pupil, their measurement in all 4928 sub-apertures and the combination
+// take 4.2 ms for the same bits.
 template <int NPX, int FFT_N, int CONV_N, int DET_N, int SPB, int WPE>
 __global__ __launch_bounds__(SPB * CONV_N) __attribute__((amdgpu_waves_per_eu(WPE))) void wfs_modes_kernel(
     const ModesLaunch q) {
